@@ -29,11 +29,37 @@
 // difference (the rounded square is monotone in |d|); the pattern itself is
 // found once, for the chosen entry.
 //
-// Work split: one wavefront per group; lane l evaluates entries l, l+64, ...
-// (each entry's error sum runs over the elements in order, so entries -- not
-// elements -- are what is parallel), then the wavefront picks the smallest
-// error with the lowest entry index, which is the sequential first minimum.
-// The group's values sit in LDS and are read as broadcasts.
+// Screening.  Scoring an entry by that definition takes 128 x 2^k distances.
+// Almost every entry is ruled out much more cheaply: with the subset sums
+// sorted (s_0 <= .. <= s_n) and m_p the midpoint of s_(p-1) and s_p,
+//     sum_j min_p (x_j - s_p)^2
+//         = sum_j (x_j - s_n)^2 - 2 sum_p (s_p - s_(p-1)) g(m_p),
+//     g(m) = sum_j max(0, m - x_j),
+// and g is one convex function per group.  The group's g is tabulated as
+// chords over ENC_CELLS equal cells of its range; a chord lies above g, so the
+// table gives a lower bound of an entry's error with one lookup per midpoint
+// instead of 128 distances per subset sum (about 300 vector instructions per
+// entry at k = 4, against 6144).  The bound is computed in binary32;
+// entry_bound() subtracts a bound on its rounding.  Entries whose lower bound exceeds the
+// error of an entry already scored can neither win nor tie and are dropped
+// (Gaussian groups keep about 5 of 1024); the others are scored in binary64,
+// first with the terms added across the lanes, then, where that leaves a
+// possible winner (within 2^-40 of the smallest), in the definition's order.
+// Every entry that could be the first minimum is scored by the definition, so
+// the result does not depend on the screening.
+//
+// Work split: one wavefront per group.  In the screening lane l takes
+// ENC_RUN consecutive entries (neighbouring entries share r and s, so the
+// divisions of Eq. 4 are made once per (r, s)); in the scoring every lane takes
+// its two elements of one entry.  Where more than ENC_LIST entries of a chunk
+// survive (degenerate groups), lanes take entries instead and the elements run
+// in order, so such a group costs what an unscreened search does.
+// Bound: vector instruction issue (about 4600 of the ~7000 per group are the
+// bounds).  Measured on a 4096 x 4096 matrix, 1024 entries, encoding and
+// packing: k = 4 17.90 -> 1.50 ms, with the encoder cache at k = 3 7.53 ->
+// 0.91 ms, against scoring every entry by the definition (with pruning).
+// Groups whose entries are all alike (magnitudes below binary16's) keep every
+// entry and take what they took: k = 4 3.17 -> 3.16 ms for 1024 x 2048.
 #include "device_ops.h"
 #include "f16_round.h"
 #include "launch.h"
@@ -49,31 +75,56 @@ __device__ __forceinline__ double f16_bits_to_double(uint16_t h)
     return (double)half_bits_to_float(h);  // both conversions exact
 }
 
-// Coefficients of one entry; false if a coefficient is not finite.
-template <int K>
-__device__ __forceinline__ bool entry_coeffs(double r, double s, double b, bool normalise, uint16_t *c)
+// binary64 -> binary16, round to nearest, ties to even: binary32 toward zero
+// with the lost bits kept in its last one (24 bits, 13 more than binary16's),
+// which the hardware's one rounding to binary16 then treats as the exact value.
+__device__ __forceinline__ uint16_t f64_to_f16_odd(double x)
 {
-    double norm = 1.0;
-    if (normalise) {
-        double a = 1.0, t = 0.0;
+    const float f = (float)x;
+    const double back = (double)f;
+    uint32_t u = (uint32_t)__float_as_int(f);
+    u -= fabs(back) > fabs(x) ? 1u : 0u;
+    u |= back != x ? 1u : 0u;
+    return __half_as_ushort(__float2half_rn(__int_as_float((int)u)));
+}
+
+// The part of an entry's coefficients that r and s fix, (s r^i) / N(r).
+template <int K>
+struct EntryShape {
+    double q[K];
+
+    __device__ __forceinline__ void set(double r, double s, bool normalise)
+    {
+        double norm = 1.0;
+        if (normalise) {
+            double a = 1.0, t = 0.0;
+#pragma unroll
+            for (int i = 0; i < K; ++i) {
+                t += fabs(a);
+                a *= r;
+            }
+            norm = t;
+        }
+        double pw = 1.0;
 #pragma unroll
         for (int i = 0; i < K; ++i) {
-            t += fabs(a);
-            a *= r;
+            q[i] = (s * pw) / norm;
+            pw *= r;
         }
-        norm = t;
     }
-    double pw = 1.0;
-    bool ok = true;
+
+    // the coefficients at bias b; false if one is not finite
+    __device__ __forceinline__ bool coeffs(double b, uint16_t *c) const
+    {
+        bool ok = true;
 #pragma unroll
-    for (int i = 0; i < K; ++i) {
-        const double v = (s * pw) / norm + b;
-        c[i] = f64_to_f16_rne(v);
-        ok = ok && (c[i] & 0x7c00u) != 0x7c00u;
-        pw *= r;
+        for (int i = 0; i < K; ++i) {
+            c[i] = f64_to_f16_odd(q[i] + b);
+            ok = ok && (c[i] & 0x7c00u) != 0x7c00u;
+        }
+        return ok;
     }
-    return ok;
-}
+};
 
 template <int K>
 __device__ __forceinline__ void subset_sums(const uint16_t *c, double *sums)
@@ -127,8 +178,6 @@ __device__ __forceinline__ double nearest_sq(const double *sums, double x)
     return m;
 }
 
-constexpr int ENC_CHUNK = 16;  // elements between pruning checks
-
 __device__ __forceinline__ double wave_min_f64(double v)
 {
 #pragma unroll
@@ -156,14 +205,341 @@ struct EncodeArgs {
     int n_ratio1, n_ratio2, n_scale, n_bias, normalise;
 };
 
-// A wavefront's LDS for one group: the group's values (read as broadcasts)
-// and the search's exchange slots.
+constexpr int ENC_CELLS = 512;                    // chords of the group's g
+constexpr int ENC_RUN = 16;                       // consecutive entries a lane screens
+constexpr int ENC_CHUNK = ENC_RUN * ENC_THREADS;  // entries screened at a time
+constexpr int ENC_LIST = 32;                      // entries scored across the lanes, at most
+// Two orders of adding 128 non-negative binary64 terms differ by less than
+// this share of their sum (2 x 127 roundings of 2^-53).
+constexpr double ENC_ORDER_EPS = 0x1p-40;
+// The screening is off (every entry is kept) where its binary32 sums might
+// overflow; coefficients are binary16, so such a group has no close entry.
+constexpr float ENC_SCREEN_MAX = 1e15f;
+
+// A wavefront's LDS for one group.
 struct EncodeLds {
-    double D[GROUP];
-    double best_mse_l[ENC_THREADS];
-    int best_e_l[ENC_THREADS];
-    double q_pair[2];
+    double D[GROUP];      // the values in element order (read as broadcasts)
+    double E[GROUP + 1];  // table build: twice the sums of the t smallest values; scoring: an
+                          // entry's terms in element order
+    float2 cell[ENC_CELLS + 2];  // chords (value at 0, slope) in m2 = 2 m; below and above the range
+    union {
+        float lb[ENC_CHUNK];   // lower bounds, entry of (lane, i) at i * 64 + lane
+        int mark[ENC_CELLS];   // table build: values up to and in each cell
+    };
+    int list[ENC_LIST];
 };
+
+// What the search knows about a group besides L (wavefront-uniform).
+struct GroupStats {
+    double mn, mx, q95;
+    float lo2, ih;  // 2 min, cells per unit of 2 x
+    float X, S2, T2;  // max |x|, sum x^2, 2 sum x
+};
+
+__device__ __forceinline__ float lane_f32(float v, int l)
+{
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+}
+
+__device__ __forceinline__ double lane_f64(double v, int l)
+{
+    const uint64_t u = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, l);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), l);
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v)
+{
+    const uint64_t u = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, 0xf, 0xf, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, 0xf, 0xf, false);
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
+// Sum over the wavefront (wavefront-uniform, in a tree's order).
+__device__ __forceinline__ double wave_sum_f64(double v)
+{
+    v += dpp_f64<DPP_QUAD_XOR1>(v);
+    v += dpp_f64<DPP_QUAD_XOR2>(v);
+    v += dpp_f64<DPP_ROW_HALF_MIRROR>(v);
+    v += dpp_f64<DPP_ROW_MIRROR>(v);
+    return (lane_f64(v, 0) + lane_f64(v, 16)) + (lane_f64(v, 32) + lane_f64(v, 48));
+}
+
+__device__ __forceinline__ float wave_min_f32(float v)
+{
+    v = fminf(v, dpp_f32<DPP_QUAD_XOR1>(v));
+    v = fminf(v, dpp_f32<DPP_QUAD_XOR2>(v));
+    v = fminf(v, dpp_f32<DPP_ROW_HALF_MIRROR>(v));
+    v = fminf(v, dpp_f32<DPP_ROW_MIRROR>(v));
+    return fminf(fminf(lane_f32(v, 0), lane_f32(v, 16)), fminf(lane_f32(v, 32), lane_f32(v, 48)));
+}
+
+// binary32 at or above a non-negative binary64 value.
+__device__ __forceinline__ float f32_above(double v) { return (float)v * (1.0f + 0x1p-20f); }
+
+// Cell of 2 m: 0 below the range, ENC_CELLS + 1 above it.
+__device__ __forceinline__ int cell_of(const GroupStats &t, float m2)
+{
+    const float u = fmaf(m2 - t.lo2, t.ih, 1.0f);
+    return (int)__builtin_amdgcn_fmed3f(u, 0.0f, (float)(ENC_CELLS + 1));
+}
+
+// Sorts the group (x0, x1: the lane's two values), takes the order statistics
+// and tabulates g.  With t values below m and P their sum, 2 g(m) = m2 t - 2 P
+// for m2 = 2 m.
+__device__ GroupStats group_table(EncodeLds &L, float x0, float x1)
+{
+    const int lane = threadIdx.x;
+    GroupStats st;
+    // bitonic sort of 128 values, sorted value 2 lane + h in v[h]; med3 with
+    // an infinity is min or max
+    float v0 = x0, v1 = x1;
+#pragma unroll
+    for (int k = 2; k <= GROUP; k <<= 1) {
+#pragma unroll
+        for (int j = k >> 1; j >= 2; j >>= 1) {
+            const bool keep_min = ((lane & (j >> 1)) == 0) == ((lane & (k >> 1)) == 0);
+            const float sel = keep_min ? -__builtin_inff() : __builtin_inff();
+            v0 = __builtin_amdgcn_fmed3f(v0, __shfl_xor(v0, j >> 1), sel);
+            v1 = __builtin_amdgcn_fmed3f(v1, __shfl_xor(v1, j >> 1), sel);
+        }
+        const bool asc = (lane & (k >> 1)) == 0;
+        const float a = fminf(v0, v1), b = fmaxf(v0, v1);
+        v0 = asc ? a : b;
+        v1 = asc ? b : a;
+    }
+    st.mn = (double)lane_f32(v0, 0);
+    st.mx = (double)lane_f32(v1, 63);
+
+    // sorted positions lo and lo+1 of the linear-interpolation percentile
+    constexpr double pos = 0.95 * (double)(GROUP - 1);
+    constexpr int lo = (int)pos;
+    const double frac = pos - (double)lo;
+    static_assert(lo % 2 == 0, "both positions in one lane");
+    const double q0 = (double)lane_f32(v0, lo / 2), q1 = (double)lane_f32(v1, lo / 2);
+    st.q95 = q0 + frac * (q1 - q0);
+
+    // twice the sums of the t smallest values
+    double incl = (double)v0 + (double)v1;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const double up = __shfl_up(incl, off);
+        incl += lane >= off ? up : 0.0;
+    }
+    double excl = __shfl_up(incl, 1);
+    excl = lane > 0 ? excl : 0.0;
+    L.E[2 * lane] = 2.0 * excl;
+    L.E[2 * lane + 1] = 2.0 * (excl + (double)v0);
+    const double total2 = 2.0 * lane_f64(incl, 63);
+    if (lane == 63)
+        L.E[GROUP] = total2;
+
+    const double range2 = 2.0 * st.mx - 2.0 * st.mn;
+    const double inv_h2 = range2 > 0.0 ? (double)ENC_CELLS / range2 : 0.0;
+    st.lo2 = 2.0f * (float)st.mn;
+    st.ih = range2 > 0.0 ? (float)fmin(inv_h2, 1e38) : 1e38f;
+    st.X = (float)fmax(fabs(st.mn), fabs(st.mx));
+    st.S2 = (float)wave_sum_f64((double)x0 * (double)x0 + (double)x1 * (double)x1);
+    st.T2 = (float)total2;
+
+    // values in and below each cell: the last value of a cell marks it, then
+    // a running maximum over the cells
+    constexpr int PER = ENC_CELLS / 64;
+    static_assert(PER == 8, "two 16-byte stores per lane");
+    *(int4 *)&L.mark[PER * lane] = make_int4(0, 0, 0, 0);
+    *(int4 *)&L.mark[PER * lane + 4] = make_int4(0, 0, 0, 0);
+    __syncthreads();
+    auto cell_in = [&](float x) { return min(max(cell_of(st, 2.0f * x) - 1, 0), ENC_CELLS - 1); };
+    const int c0 = cell_in(v0), c1 = cell_in(v1), c2 = __shfl_down(c0, 1);
+    if (c0 != c1)
+        L.mark[c0] = 2 * lane + 1;
+    if (lane == 63 || c1 != c2)
+        L.mark[c1] = 2 * lane + 2;
+    __syncthreads();
+    int n[PER];
+    *(int4 *)&n[0] = *(const int4 *)&L.mark[PER * lane];
+    *(int4 *)&n[4] = *(const int4 *)&L.mark[PER * lane + 4];
+#pragma unroll
+    for (int i = 1; i < PER; ++i)
+        n[i] = max(n[i], n[i - 1]);
+    int below = n[PER - 1];
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int up = __shfl_up(below, off);
+        below = max(below, lane >= off ? up : 0);
+    }
+    below = __shfl_up(below, 1);
+    below = lane > 0 ? below : 0;
+
+    const double h2 = range2 / (double)ENC_CELLS, lo2 = 2.0 * st.mn;
+    double u = lo2 + (double)(PER * lane) * h2;
+    double g = u * (double)below - L.E[below];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const int t = max(below, n[i]);
+        const double un = lo2 + (double)(PER * lane + i + 1) * h2;
+        const double gn = un * (double)t - L.E[t];
+        const double slope = (gn - g) * inv_h2;
+        L.cell[1 + PER * lane + i] = make_float2((float)(g - slope * u), (float)slope);
+        u = un;
+        g = gn;
+    }
+    if (lane == 0) {
+        L.cell[0] = make_float2(0.0f, 0.0f);
+        L.cell[ENC_CELLS + 1] = make_float2((float)-total2, (float)GROUP);
+    }
+    __syncthreads();
+    return st;
+}
+
+// s[0 .. 2n) sorted from two sorted halves of n (odd-even merge).
+template <int N>
+__device__ __forceinline__ void merge_sorted(float *s)
+{
+    auto exchange = [&](int i, int j) {
+        const float a = fminf(s[i], s[j]), b = fmaxf(s[i], s[j]);
+        s[i] = a;
+        s[j] = b;
+    };
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+        exchange(i, i + N);
+#pragma unroll
+    for (int j = N / 2; j > 0; j >>= 1)
+#pragma unroll
+        for (int i = j; i + j < 2 * N; i += 2 * j)
+#pragma unroll
+            for (int q = 0; q < j; ++q)
+                exchange(i + q, i + q + j);
+}
+
+// A lower bound of sum_j min_p (x_j - s_p)^2 for coefficients c: the chord
+// table's value (see the top of the file) less a bound on its rounding.
+//
+// With u = 2^-24, A = max |s_p|, W = s_n - s_0, X = max |x| and Z = X + A, the
+// binary32 roundings move the result by at most u times
+//   the subset sums (three additions)                       768 A Z
+//   midpoints (256 W A), gaps s_p - s_(p-1) (256 W Z)
+//   the cell: 2 m and the values are placed to within 12 u X, and slopes
+//     differ by at most 128 (a neighbour's chord, a value counted one cell
+//     off)                                                  2 x 1536 W X
+//   the chord's slope, value at 0 and result                1024 W Z
+//   four running sums of the gaps' products, their total    1536 W Z + 768 Z^2
+//   the sum about s_n and the difference                    640 Z^2 + 256 W Z
+// which is less than 2300 Z^2 + 6700 W Z.
+template <int K>
+__device__ __forceinline__ float entry_bound(const EncodeLds &L, const GroupStats &t, const uint16_t *c)
+{
+    constexpr int NS = 1 << K;
+    float s[NS];
+    s[0] = 0.0f;
+    auto add_plane = [&](auto n_, uint16_t ci) {
+        constexpr int N = decltype(n_)::value;
+        const float f = half_bits_to_float(ci);
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+            s[N + i] = s[i] + f;
+        merge_sorted<N>(s);
+    };
+    add_plane(std::integral_constant<int, 1>{}, c[0]);
+    if constexpr (K > 1)
+        add_plane(std::integral_constant<int, 2>{}, c[1]);
+    if constexpr (K > 2)
+        add_plane(std::integral_constant<int, 4>{}, c[2]);
+    if constexpr (K > 3)
+        add_plane(std::integral_constant<int, 8>{}, c[3]);
+    float acc[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int p = 1; p < NS; ++p) {
+        const float m2 = s[p] + s[p - 1], gap = s[p] - s[p - 1];
+        const float2 ch = L.cell[cell_of(t, m2)];
+        acc[p & 3] = fmaf(gap, fmaf(ch.y, m2, ch.x), acc[p & 3]);
+    }
+    const float sn = s[NS - 1], W = sn - s[0];
+    const float Z = t.X + fmaxf(fabsf(s[0]), fabsf(sn));
+    const float about = fmaf((float)GROUP * sn, sn, fmaf(-sn, t.T2, t.S2));
+    const float tol = 0x1p-24f * Z * fmaf(2300.f, Z, 6700.f * W);
+    return t.X > ENC_SCREEN_MAX ? -3e38f : about - ((acc[0] + acc[1]) + (acc[2] + acc[3])) - tol;
+}
+
+// Scores the lanes' coefficient sets c (`want`: the lane has one, `v`: its
+// lower bound) on the group.  Every set whose error may be the smallest of
+// them, or equal to it, and at most `ub` gets its MSE by the definition's
+// order; the others (and lanes without a set) return infinity.  ub: an upper
+// bound on the error sum of interest, lowered to the smallest one found.
+template <int K>
+__device__ double score_lanes(EncodeLds &L, const uint16_t *c, bool want, float v, double d0, double d1, double &ub)
+{
+    const int lane = threadIdx.x;
+    double mse = __builtin_inf();
+    uint64_t left = __ballot(want && !(v > f32_above(ub)));
+    if (__popcll(left) > ENC_LIST) {  // many: a lane per set, the elements in order
+        if (want) {
+            double sums[1 << K];
+            subset_sums<K>(c, sums);
+            mse = entry_mse<K>(L.D, sums);
+        }
+        ub = fmin(ub, wave_min_f64(mse) * (double)GROUP * (1.0 + ENC_ORDER_EPS));
+        return mse;
+    }
+    uint32_t w[(K + 1) / 2];
+#pragma unroll
+    for (int i = 0; i < (K + 1) / 2; ++i)
+        w[i] = (uint32_t)c[2 * i] | (2 * i + 1 < K ? (uint32_t)c[2 * i + 1] << 16 : 0u);
+    // the terms of the lane's two elements for the set of lane q
+    auto terms = [&](int q, double &e0, double &e1) {
+        uint16_t cq[K];
+#pragma unroll
+        for (int i = 0; i < K; ++i) {
+            const uint32_t wq = (uint32_t)__builtin_amdgcn_readlane((int)w[i / 2], q);
+            cq[i] = (uint16_t)(i & 1 ? wq >> 16 : wq & 0xffffu);
+        }
+        double sums[1 << K];
+        subset_sums<K>(cq, sums);
+        e0 = nearest_sq<K>(sums, d0);
+        e1 = nearest_sq<K>(sums, d1);
+    };
+    double tsum = __builtin_inf();
+    bool first = true;
+    while (left) {
+        int q = __ffsll((unsigned long long)left) - 1;
+        if (first) {  // the lowest bound first: its error drops most of the others
+            const float vm = wave_min_f32((left >> lane) & 1 ? v : __builtin_inff());
+            const uint64_t at = __ballot(((left >> lane) & 1) && v == vm);
+            q = at ? __ffsll((unsigned long long)at) - 1 : q;
+            first = false;
+        }
+        double e0, e1;
+        terms(q, e0, e1);
+        const double s = wave_sum_f64(e0 + e1);
+        if (lane == q)
+            tsum = s;
+        ub = fmin(ub, s * (1.0 + ENC_ORDER_EPS));
+        left &= ~(1ull << q);
+        left &= __ballot(!(v > f32_above(ub)));
+    }
+    left = __ballot(tsum * (1.0 - ENC_ORDER_EPS) <= ub && tsum < __builtin_inf());
+    while (left) {
+        const int q = __ffsll((unsigned long long)left) - 1;
+        left &= left - 1;
+        double e0, e1;
+        terms(q, e0, e1);
+        __syncthreads();  // the last reads of E are done
+        L.E[lane] = e0;
+        L.E[lane + 64] = e1;
+        __syncthreads();
+        double err = 0.0;
+#pragma unroll 16
+        for (int j = 0; j < GROUP; ++j)
+            err += L.E[j];
+        if (lane == q)
+            mse = err / (double)GROUP;
+    }
+    return mse;
+}
 
 template <int K>
 struct GroupChoice {
@@ -181,46 +557,19 @@ __device__ __forceinline__ int wave_min_int(int v)
 }
 
 // Algorithm 1 over the group in L.D (d0, d1: the lane's elements lane and
-// lane + 64).  Every lane returns the same choice.
+// lane + 64; st and L.cell: group_table's).  Every lane returns the same choice.
 template <int K>
-__device__ GroupChoice<K> search_group(const EncodeArgs &a, EncodeLds &L, double d0, double d1)
+__device__ GroupChoice<K> search_group(const EncodeArgs &a, EncodeLds &L, const GroupStats &st, double d0, double d1)
 {
     const int lane = threadIdx.x;
-    const double *D = L.D;
-    // statistics in element order (every lane, from broadcast reads)
-    double mn = D[0], mx = D[0], sum = 0.0;
-    for (int j = 0; j < GROUP; ++j) {
-        const double v = D[j];
-        if (v < mn)
-            mn = v;
-        if (v > mx)
-            mx = v;
-        sum += v;
-    }
+    double sum = 0.0;  // in element order
+#pragma unroll 16
+    for (int j = 0; j < GROUP; ++j)
+        sum += L.D[j];
     const double avg = sum / (double)GROUP;
 
-    // sorted positions lo and lo+1 of the linear-interpolation percentile:
-    // stable rank of each of the lane's two elements
-    const double pos = 0.95 * (double)(GROUP - 1);
-    const int lo = (int)floor(pos);
-    const double frac = pos - (double)lo;
-    {
-        int r0 = 0, r1 = 0;
-        for (int j = 0; j < GROUP; ++j) {
-            const double v = D[j];
-            r0 += (v < d0) || (v == d0 && j < lane);
-            r1 += (v < d1) || (v == d1 && j < lane + 64);
-        }
-        if (r0 == lo || r0 == lo + 1)
-            L.q_pair[r0 - lo] = d0;
-        if (r1 == lo || r1 == lo + 1)
-            L.q_pair[r1 - lo] = d1;
-    }
-    __syncthreads();
-    const double q95 = L.q_pair[0] + frac * (L.q_pair[1] - L.q_pair[0]);
-
-    const double s_max = 1.1 * (mx - mn);
-    const double s_min = 2.0 * q95;
+    const double s_max = 1.1 * (st.mx - st.mn);
+    const double s_min = 2.0 * st.q95;
     const double s_gran = (s_max - s_min) / (double)a.n_scale;
     const double b_max = 2.0 * fabs(avg) / (double)K;
     const double b_min = -b_max;
@@ -230,102 +579,133 @@ __device__ GroupChoice<K> search_group(const EncodeArgs &a, EncodeLds &L, double
     const int per_r = a.n_scale * a.n_bias;
     const int n_entries = (a.n_ratio1 + a.n_ratio2) * per_r;
 
-    auto entry_rsb = [&](int e, double &r, double &s, double &b) {
-        const int ir = e / per_r, js = (e / a.n_bias) % a.n_scale, kb = e % a.n_bias;
-        r = ir < a.n_ratio1 ? -1.0 + (double)(ir + 1) * r1_gran : -2.0 + (double)(ir - a.n_ratio1) * r2_gran;
-        s = s_min + (double)(js + 1) * s_gran;
-        b = b_min + (double)kb * b_gran;
+    auto ratio_of = [&](int ir) {
+        return ir < a.n_ratio1 ? -1.0 + (double)(ir + 1) * r1_gran : -2.0 + (double)(ir - a.n_ratio1) * r2_gran;
+    };
+    auto scale_of = [&](int js) { return s_min + (double)(js + 1) * s_gran; };
+    auto bias_of = [&](int kb) { return b_min + (double)kb * b_gran; };
+    // an entry's coefficients; false if it is not admissible
+    auto entry_at = [&](int e, uint16_t *c) {
+        const double s = scale_of((e / a.n_bias) % a.n_scale);
+        EntryShape<K> sh;
+        sh.set(ratio_of(e / per_r), s, a.normalise != 0);
+        return s > 0.0 && sh.coeffs(bias_of(e % a.n_bias), c);
     };
 
-    // Pruning (exact): an entry's error sum only grows as elements are added
-    // (the terms are >= 0 and rounding is monotone), so once err / n exceeds
-    // the smallest MSE any lane has completed, the entry's final MSE is
-    // strictly larger than that and it can neither win nor tie; its remaining
-    // elements are skipped.  Lanes share their best MSE after every round of
-    // 64 entries.
-    //
-    // Seed for the pruning bound: one round of entries spread over the grid
-    // (lane l: ratio l mod |R|, the middle bias, scales spread over the
-    // range), each scored over all elements.  Their smallest MSE is an upper
-    // bound on the search's minimum (they are entries of the grid), so
-    // pruning against it from the first round on stays exact; the search
-    // below scores every entry it does not prune, these included, so the
-    // result does not depend on the seed.
-    double shared_best = __builtin_inf();
-    if (n_entries > ENC_THREADS) {
-        const int n_r = a.n_ratio1 + a.n_ratio2;
-        const int ir = lane % n_r;
-        const int per_lane_r = (ENC_THREADS + n_r - 1) / n_r;  // lanes sharing a ratio
-        const int js = ((lane / n_r) * a.n_scale + a.n_scale / 2) / per_lane_r % a.n_scale;
-        const int e = (ir * a.n_scale + js) * a.n_bias + a.n_bias / 2;
-        double r, sc, b;
-        entry_rsb(e, r, sc, b);
-        uint16_t c[K];
-        double mse = __builtin_inf();
-        if (sc > 0.0 && entry_coeffs<K>(r, sc, b, a.normalise != 0, c)) {
+    double best_mse = __builtin_inf(), ub = __builtin_inf();  // ub: on the smallest error sum
+    int best_e = -1;
+    for (int e0 = 0; e0 < n_entries; e0 += ENC_CHUNK) {
+        const int left = n_entries - e0;
+        const int run = min(ENC_RUN, (left + ENC_THREADS - 1) / ENC_THREADS);
+        // lower bounds of the lane's run of entries
+        float vmin = __builtin_inff();
+        int emin = -1;
+        {
+            const int e1 = e0 + lane * run;
+            int ir = e1 / per_r, js = (e1 / a.n_bias) % a.n_scale, kb = e1 % a.n_bias;
+            double s = 0.0;
+            EntryShape<K> sh;
+            for (int i = 0; i < run; ++i) {
+                float v = __builtin_inff();
+                if (e1 + i < n_entries) {
+                    if (i == 0 || kb == 0) {
+                        s = scale_of(js);
+                        sh.set(ratio_of(ir), s, a.normalise != 0);
+                    }
+                    uint16_t c[K];
+                    if (s > 0.0 && sh.coeffs(bias_of(kb), c)) {
+                        v = entry_bound<K>(L, st, c);
+                        if (emin < 0 || v < vmin) {
+                            vmin = v;
+                            emin = e1 + i;
+                        }
+                    }
+                    if (++kb == a.n_bias) {
+                        kb = 0;
+                        if (++js == a.n_scale) {
+                            js = 0;
+                            ++ir;
+                        }
+                    }
+                }
+                L.lb[i * ENC_THREADS + lane] = v;
+            }
+        }
+        // the entry with the lowest bound, scored: its error drops most others
+        const uint64_t have = __ballot(emin >= 0);
+        if (have == 0)  // no admissible entry in this chunk
+            continue;
+        const float vm = wave_min_f32(vmin);
+        const uint64_t at = __ballot(emin >= 0 && vmin == vm);
+        const int es = __builtin_amdgcn_readlane(emin, __ffsll((unsigned long long)(at ? at : have)) - 1);
+        {
+            uint16_t c[K];
+            entry_at(es, c);
             double sums[1 << K];
             subset_sums<K>(c, sums);
-            mse = entry_mse<K>(D, sums);
+            ub = fmin(ub, wave_sum_f64(nearest_sq<K>(sums, d0) + nearest_sq<K>(sums, d1)) * (1.0 + ENC_ORDER_EPS));
         }
-        shared_best = wave_min_f64(mse);
-    }
-    double best_mse = __builtin_inf();
-    int best_e = -1;
-    for (int e0 = 0; e0 < n_entries; e0 += ENC_THREADS) {
-        const int e = e0 + lane;
-        bool ok = false;
-        double sums[1 << K];
-        if (e < n_entries) {
-            double r, s, b;
-            entry_rsb(e, r, s, b);
-            uint16_t c[K];
-            ok = s > 0.0 && entry_coeffs<K>(r, s, b, a.normalise != 0, c);
-            if (ok)
-                subset_sums<K>(c, sums);
+        // entries that may win or tie (an inadmissible one has v = infinity)
+        auto kept = [&](int i) {
+            const float v = L.lb[i * ENC_THREADS + lane];
+            return !(v > f32_above(ub)) && v < __builtin_inff();
+        };
+        int n = 0;
+        for (int i = 0; i < run; ++i) {
+            const bool k = kept(i);
+            const uint64_t m = __ballot(k);
+            const int slot = n + __popcll(m & ((1ull << lane) - 1));
+            if (k && slot < ENC_LIST)
+                L.list[slot] = e0 + lane * run + i;
+            n += __popcll(m);
         }
-        if (ok) {
-            double err = 0.0;
-            bool pruned = false;
-            for (int j0 = 0; j0 < GROUP; j0 += ENC_CHUNK) {
+        __syncthreads();
+        double mse = __builtin_inf();
+        int e = -1;
+        if (n <= ENC_LIST) {
+            uint16_t c[K] = {};
+            float v = __builtin_inff();
+            if (lane < n) {
+                e = L.list[lane];
+                entry_at(e, c);
+                v = L.lb[(e - e0) % run * ENC_THREADS + (e - e0) / run];
+            }
+            mse = score_lanes<K>(L, c, lane < n, v, d0, d1, ub);
+        } else {  // a lane per entry, the elements in order
+            for (int i = 0; i < run; ++i) {
+                uint16_t c[K];
+                const int ei = e0 + lane * run + i;
+                double m = __builtin_inf();
+                if (kept(i) && entry_at(ei, c)) {
+                    double sums[1 << K];
+                    subset_sums<K>(c, sums);
+                    double err = 0.0;
+                    for (int j0 = 0; j0 < GROUP && err <= ub; j0 += 16)
 #pragma unroll 4
-                for (int j = j0; j < j0 + ENC_CHUNK; ++j) {
-                    err += nearest_sq<K>(sums, D[j]);
+                        for (int j = j0; j < j0 + 16; ++j)
+                            err += nearest_sq<K>(sums, L.D[j]);
+                    if (err <= ub)  // (else it can neither win nor tie)
+                        m = err / (double)GROUP;
                 }
-                if (err / (double)GROUP > shared_best) {
-                    pruned = true;
-                    break;
+                if (m < mse) {
+                    mse = m;
+                    e = ei;
                 }
-            }
-            if (!pruned) {
-                const double mse = err / (double)GROUP;
-                if (mse < best_mse) {
-                    best_mse = mse;
-                    best_e = e;
-                }
+                ub = fmin(ub, wave_min_f64(m) * (double)GROUP);
             }
         }
-        shared_best = wave_min_f64(fmin(shared_best, best_mse));
-    }
-    L.best_mse_l[lane] = best_mse;
-    L.best_e_l[lane] = best_e;
-    __syncthreads();
-    // smallest error, lowest entry index among equal errors
-    double m = __builtin_inf();
-    int be = -1;
-    for (int l = 0; l < ENC_THREADS; ++l) {
-        const int e = L.best_e_l[l];
-        const double v = L.best_mse_l[l];
-        if (e >= 0 && (be < 0 || v < m || (v == m && e < be))) {
-            m = v;
-            be = e;
+        // smallest error, lowest entry index among equal errors
+        const double m = wave_min_f64(mse);
+        if (m < best_mse) {  // (an equal one of an earlier chunk comes first)
+            best_mse = m;
+            best_e = wave_min_int(mse == m ? e : INT_MAX);
         }
+        __syncthreads();  // lb and list are read before the next chunk's
     }
 
     GroupChoice<K> out;
-    if (be >= 0) {
-        double r, s, b;
-        entry_rsb(be, r, s, b);
-        entry_coeffs<K>(r, s, b, a.normalise != 0, out.c);
+    if (best_e >= 0) {
+        entry_at(best_e, out.c);
     } else {  // no admissible entry
         out.c[0] = f64_to_f16_rne(avg);
 #pragma unroll
@@ -333,10 +713,10 @@ __device__ GroupChoice<K> search_group(const EncodeArgs &a, EncodeLds &L, double
             out.c[i] = 0;
         double sums[1 << K];
         subset_sums<K>(out.c, sums);
-        m = entry_mse<K>(D, sums);
+        best_mse = entry_mse<K>(L.D, sums);
     }
-    out.mse = m;
-    out.entry = be;
+    out.mse = best_mse;
+    out.entry = best_e;
     return out;
 }
 
@@ -375,11 +755,12 @@ __global__ void __launch_bounds__(ENC_THREADS) encode_kernel(EncodeArgs a)
     const size_t o = grp / G, g = grp % G;
     const float *src = a.W + o * (size_t)a.I + g * GROUP;
 
-    const double d0 = (double)src[lane], d1 = (double)src[lane + 64];
+    const float x0 = src[lane], x1 = src[lane + 64];
+    const double d0 = (double)x0, d1 = (double)x1;
     L.D[lane] = d0;
     L.D[lane + 64] = d1;
-    __syncthreads();
-    const GroupChoice<K> r = search_group<K>(a, L, d0, d1);
+    const GroupStats st = group_table(L, x0, x1);
+    const GroupChoice<K> r = search_group<K>(a, L, st, d0, d1);
     store_group<K>(a, grp, r.c, d0, d1, r.mse);
 }
 
@@ -388,7 +769,7 @@ __global__ void __launch_bounds__(ENC_THREADS) encode_kernel(EncodeArgs a)
 // s (a coefficient set the full search chose for one of the row's last
 // `slots` searched groups, and that group's insertion number; the oldest set
 // is replaced first).  For each group every held set is scored with the
-// search's MSE (one set per lane, the elements in order); the smallest --
+// search's MSE (screened like the entries of a search); the smallest --
 // the oldest among equal ones -- is taken if it is strictly below the mean
 // MSE of the row's earlier groups (binary64 sum in group order over their
 // count), otherwise the full search runs and its choice enters the cache
@@ -411,22 +792,22 @@ __global__ void __launch_bounds__(ENC_THREADS) encode_cached_kernel(EncodeArgs a
     for (int g = 0; g < G; ++g) {
         const size_t grp = o * G + g;
         const float *src = a.W + o * (size_t)a.I + (size_t)g * GROUP;
-        const double d0 = (double)src[lane], d1 = (double)src[lane + 64];
+        const float x0 = src[lane], x1 = src[lane + 64];
+        const double d0 = (double)x0, d1 = (double)x1;
         __syncthreads();  // the previous group's reads of L are done
         L.D[lane] = d0;
         L.D[lane + 64] = d1;
-        __syncthreads();
+        const GroupStats st = group_table(L, x0, x1);
         bool hit = false;
         uint16_t c[K];
         double mse = 0.0;
         if (g > 0 && n_cached > 0) {
             const double avg = mse_sum / (double)g;
-            double m = __builtin_inf();
-            if (lane < n_cached) {
-                double sums[1 << K];
-                subset_sums<K>(cs, sums);
-                m = entry_mse<K>(L.D, sums);
-            }
+            // a set whose lower bound is above the mean cannot be taken
+            const bool held = lane < n_cached;
+            const float v = held ? entry_bound<K>(L, st, cs) : __builtin_inff();
+            double ub = avg * (double)GROUP;
+            const double m = score_lanes<K>(L, cs, held, v, d0, d1, ub);
             const double best = wave_min_f64(m);
             if (best < avg) {  // wavefront-uniform
                 const int oldest = wave_min_int(lane < n_cached && m == best ? seq : INT_MAX);
@@ -439,7 +820,7 @@ __global__ void __launch_bounds__(ENC_THREADS) encode_cached_kernel(EncodeArgs a
             }
         }
         if (!hit) {
-            const GroupChoice<K> r = search_group<K>(a, L, d0, d1);
+            const GroupChoice<K> r = search_group<K>(a, L, st, d0, d1);
 #pragma unroll
             for (int i = 0; i < K; ++i)
                 c[i] = r.c[i];

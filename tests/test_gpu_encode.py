@@ -84,6 +84,37 @@ def test_encoder_bit_exact_degenerate_groups(sb):
         assert_same(sb, W, k, what="degenerate")
 
 
+def screening_rows(kind, n, rng):
+    """n values that stress the search's screening: the lower bounds of an
+    entry come from a table over the group's range, so wide ranges, values
+    crowded into a few table cells, ties and the edges of binary32 matter."""
+    z = rng.standard_normal(n)
+    return {"cauchy": np.clip(0.01 * z / rng.standard_normal(n), -1e4, 1e4),
+            "grid": np.round(3 * z) * 0.01,
+            "ternary": np.sign(z) * (np.abs(z) > 0.5) * 0.02,
+            "clusters": np.where(z > 0, 0.5, -0.5) + 1e-3 * rng.standard_normal(n),
+            "offset": -1 + 0.01 * z,
+            "spikes": np.where(rng.random(n) < 0.01, 100 * z, 0.02 * z),
+            "half_zero": np.maximum(0.02 * z, 0.0),
+            "binary16_subnormal": 1e-6 * z,
+            "all_entries_equal": 1e-30 * z,
+            "binary32_subnormal": 1e-41 * z,
+            "no_screening": np.where(rng.random(n) < 0.01, 1e16 * np.abs(z), 0.02 * z),
+            "overflowing": 1e38 * np.clip(z, -3, 3)}[kind]
+
+
+@pytest.mark.parametrize("kind", ["cauchy", "grid", "ternary", "clusters", "offset", "spikes", "half_zero",
+                                  "binary16_subnormal", "all_entries_equal", "binary32_subnormal", "no_screening",
+                                  "overflowing"])
+def test_encoder_screening_keeps_the_minimum(sb, kind):
+    W = screening_rows(kind, 6 * 512, np.random.default_rng(11)).astype(np.float32).reshape(6, 512)
+    for k in (1, 2, 3, 4):
+        assert_same(sb, W, k, what=kind)
+    # more than one chunk of entries (2304), the last one partial
+    assert_same(sb, W[:2], 4, oracle.SearchParams(6, 6, 32, 6), what=kind)
+    assert_same_cached(sb, W, 4, 64, what=kind)
+
+
 def test_encoder_output_gemv_parity(sb):
     """The GPU-encoded matrix through the GPU GEMV against the oracle's exact
     GEMV of the same encoding."""
