@@ -416,7 +416,7 @@ def prefill_summary(trace_csv: str) -> str:
         dec, lib, fus = segs[6 * i + 3: 6 * i + 6]
         d = np.mean([x for x, n in dec if "decompress_kernel" in n]) / 1e3
         lb = sum(x for x, n in lib if "sbvr::" not in n) / PREFILL_PROBE_CALLS / 1e3
-        fu = np.mean([x for x, n in fus if "prefill_kernel" in n or "prefill_long_kernel" in n]) / 1e3
+        fu = np.mean([x for x, n in fus if "prefill_kernel" in n or "prefill_short_kernel" in n]) / 1e3
         lines.append(f"| {label} | {T} | {d:.1f} | {lb:.1f} | {d + lb:.1f} | {fu:.1f} |")
         rec[f"{label} T={T}"] = {"decompress_us": round(d, 2), "library_us": round(lb, 2), "fused_us": round(fu, 2)}
     lines += ["", "prefill-record: " + json.dumps(rec, sort_keys=True)]

@@ -75,19 +75,6 @@ __device__ __forceinline__ double f16_bits_to_double(uint16_t h)
     return (double)half_bits_to_float(h);  // both conversions exact
 }
 
-// binary64 -> binary16, round to nearest, ties to even: binary32 toward zero
-// with the lost bits kept in its last one (24 bits, 13 more than binary16's),
-// which the hardware's one rounding to binary16 then treats as the exact value.
-__device__ __forceinline__ uint16_t f64_to_f16_odd(double x)
-{
-    const float f = (float)x;
-    const double back = (double)f;
-    uint32_t u = (uint32_t)__float_as_int(f);
-    u -= fabs(back) > fabs(x) ? 1u : 0u;
-    u |= back != x ? 1u : 0u;
-    return __half_as_ushort(__float2half_rn(__int_as_float((int)u)));
-}
-
 // The part of an entry's coefficients that r and s fix, (s r^i) / N(r).
 template <int K>
 struct EntryShape {

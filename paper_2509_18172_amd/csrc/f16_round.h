@@ -45,6 +45,19 @@ __device__ __forceinline__ uint16_t f64_to_f16_rne(double x)
     return (uint16_t)(sign | (uint32_t)q);  // q == 0x400 is the smallest normal
 }
 
+// The same value for finite x without branches: binary32 toward zero with the
+// lost bits kept in its last one (24 bits, 13 more than binary16's), which the
+// hardware's one rounding to binary16 then treats as the exact value.
+__device__ __forceinline__ uint16_t f64_to_f16_odd(double x)
+{
+    const float f = (float)x;
+    const double back = (double)f;
+    uint32_t u = (uint32_t)__float_as_int(f);
+    u -= fabs(back) > fabs(x) ? 1u : 0u;
+    u |= back != x ? 1u : 0u;
+    return __half_as_ushort(__float2half_rn(__int_as_float((int)u)));
+}
+
 // Unbiased exponent of a binary16 bit pattern (subnormals as -14).
 __device__ __forceinline__ int f16_exp(uint32_t h)
 {

@@ -7,50 +7,44 @@
 // group's coefficients (Sec. 4.1), the same value sbvr_decompress writes, so
 // the result equals X times the decompressed matrix with fp32 accumulation.
 //
-// Work split.  A wavefront owns 16 weight rows (one column tile of the
-// matrix-core instruction), BTT token tiles of 16 (BTT = 1, 2, 4, 8) and a
-// run of whole groups of the inner dimension (a K-slice).  A workgroup of 16
-// wavefronts holds R = 16 / S row tiles times S K-slices; the S partial sums
-// of a row tile are added through LDS at the end in a fixed order.  Per group
-//   * the R wavefronts of a K-slice stage the group's activation tile
-//     (16 BTT tokens x 128 values) in LDS with coalesced 16-byte loads, double
-//     buffered, so the activations are read once per workgroup rather than
-//     once per row tile;
-//   * a wavefront builds the 2^k-entry subset-sum table of each of its 16 rows
-//     in its own LDS region (binary32 sums, exact when the coefficients span at
-//     most 12 binades, else binary64; rounded once to binary16);
-//   * per 32-element step (word ks of each plane) it forms the k-bit subset
-//     index of the lane's eight consecutive elements from the plane words (the
-//     device bit layout puts element 8v+p of a word at bit 4p+v, so
-//     (w >> v) & 0x11111111 holds bit i of elements 8v..8v+7 in nibbles
-//     0..7), looks them up, and multiplies the eight binary16 weights with the
-//     BTT token tiles on v_mfma_f32_16x16x32_f16 (lane l: row or column
-//     l % 16, k = 8 (l / 16) .. +7; measured on the device).
-// The plane slots, coefficients and activations of the next group are loaded
-// while the current one is decoded.
-// Bound: the decoding (about 300 vector instructions per wavefront and group,
-// whatever BTT is); BTT = 8 amortises it over 128 tokens.  From 96 tokens,
-// where its grid fills the chip, the long-prompt kernel further down runs
-// instead (32 x 32 products, 32-row column tiles).
-#include "device_ops.h"
-#include "lds_lookup.h"
-#include "f16_round.h"
+// Two kernels, both decoding in registers (row_decode.h): a lane holds the
+// subset-sum table of one weight row and the subset indices of its elements of
+// a group, looks up eight weights per step with byte permutes and feeds them
+// to the matrix cores as the B operand; the activations, staged in LDS by
+// direct loads, are the A operand.  The groups of the inner dimension are
+// split into K-slices over wavefronts, whose partial sums are added through
+// LDS in a fixed order.
+//
+//   * prefill_kernel: v_mfma_f32_32x32x16_f16.  A wavefront owns RT column
+//     tiles of 32 weight rows, TT token tiles of 32 and one K-slice; a
+//     workgroup of eight holds R row groups times S = 8 / R K-slices, the R
+//     wavefronts of a K-slice sharing its activations.
+//   * prefill_short_kernel: v_mfma_f32_16x16x32_f16.  A workgroup owns one
+//     tile of 16 weight rows and TT token tiles of 16, a wavefront per K-slice:
+//     twice the workgroups per matrix and half the decoding per wavefront and
+//     group, for prompts up to about 32 tokens and small matrices.
+//
+// What bounds them: vector instruction issue.  A wavefront decodes 32 rows x
+// 128 weights with about 350 instructions (k = 4; 132 byte permutes at 4.5
+// cycles each, most of the others at 2.6-4), beside 8 matrix-core instructions
+// per 32 tokens; at 512 tokens the two are about equal and the clock (1.75-1.9
+// GHz under this load) sets the time.  The earlier kernels looked every weight
+// up in an LDS table: random 2-byte reads at 6 LDS cycles per 64 lanes and CU
+// or more, which the four SIMDs of a CU share.  Llama-3-8B shapes, k = 4, back
+// to back over rotating weights, before -> after (us):
+//   tokens            1            37           128          512
+//   4096 x 4096     10.9 -> 6.7  17.5 -> 10.3  26.7 -> 13.8  53.6 -> 29.9
+//   1024 x 4096     10.3 -> 5.9  11.0 -> 7.0   14.9 -> 10.2  26.7 -> 16.8
+//   14336 x 4096    29.1 -> 15.4 50.0 -> 19.1  52.2 -> 30.0  120 -> 75
+//   4096 x 14336    27.3 -> 14.9 47.3 -> 25.0  80.0 -> 36.6  166 -> 92
 #include "launch.h"
+#include "row_decode.h"
 
 namespace sbvr {
 
-typedef _Float16 v8h __attribute__((ext_vector_type(8)));
-
-constexpr int PF_WAVES = 16;          // wavefronts per workgroup: R row tiles x S K-slices
-constexpr int PF_XROW = 256 + 16;     // LDS bytes per token row of an activation tile (padding
-                                      // spreads the 16 rows of an operand read over all banks)
-// subset-sum table rows padded by two entries (consecutive rows start one
-// LDS bank apart; 0, 2 and 4 measured the same)
-constexpr int PF_LUT_PAD = 2;
-// activation chunks (16 bytes) per thread and group, at most: the launcher
-// keeps S BTT <= 4 pf_xpt(BTT) (a K-slice's 1024 / S threads load 256 BTT chunks)
-__host__ __device__ constexpr int pf_xpt(int btt) { return btt <= 2 ? 4 : 2; }
 constexpr size_t PF_LDS_MAX = 160 * 1024;  // LDS of one workgroup on gfx950
+constexpr int PF_WAVES = 8;                // wavefronts of a prefill_kernel workgroup
+constexpr int PF_CUS = 256;
 
 struct PrefillArgs {
     const uint32_t *planes;  // device plane blocks
@@ -58,303 +52,88 @@ struct PrefillArgs {
     const uint16_t *X;       // binary16 [T][I]
     uint16_t *Y;             // binary16 [T][O]
     int O, I, T, n_tiles, n_gblocks, G, gps;  // gps: groups per K-slice
-    int S;                                    // K-slices per workgroup (a power of two)
 };
-
-// LDS: per K-slice two activation tiles of 16 BTT token rows (PF_XROW bytes
-// each: the group's 128 binary16 values), then per wavefront its 16 rows x
-// 2^k subset-sum table.  The K-slice reduction reuses the front afterwards.
-__host__ __device__ constexpr int pf_xtile(int btt) { return 16 * btt * PF_XROW; }
-
-template <int K, int BTT>
-__global__ void __launch_bounds__(64 * PF_WAVES) prefill_kernel(PrefillArgs a)
-{
-    constexpr int TR = tile_rows(K), NSUB = 1 << K;
-    constexpr int LROW = NSUB + PF_LUT_PAD;  // table row stride (binary16 entries)
-    constexpr int LUT_B = 16 * LROW * 2;
-    constexpr int XT = pf_xtile(BTT);
-    constexpr int XCH = 16 * BTT * 16;  // 16-byte chunks of an activation tile
-    constexpr int XPT = pf_xpt(BTT);
-    extern __shared__ __align__(16) unsigned char smem[];
-    const int lane = threadIdx.x & 63, w = wave_id();
-    const int S = a.S, R = PF_WAVES / S;
-    const int ks_id = w % S, rt = w / S;  // K-slice and row tile of this wavefront
-    const int n = lane & 15, kq = lane >> 4;
-    unsigned char *xbuf = smem + (size_t)ks_id * 2 * XT;
-    uint16_t *lut = (uint16_t *)(smem + (size_t)S * 2 * XT + w * LUT_B);
-    const int o_base = (blockIdx.x * R + rt) * 16, t_base = blockIdx.y * 16 * BTT;
-    const int g0 = ks_id * a.gps;
-    const int rows_dev = a.n_tiles * TR;  // rows held by the device format (padding included)
-
-    v4f acc[BTT];
-#pragma unroll
-    for (int tt = 0; tt < BTT; ++tt)
-        acc[tt] = v4f{0.f, 0.f, 0.f, 0.f};
-
-    // the decode row of this lane (its column of the result)
-    const int o = min(o_base + n, rows_dev - 1);
-    const bool row_ok = o_base + n < rows_dev;
-    const int tile = o / TR, r = o % TR;
-    struct GroupLoads {
-        uint4 slot[K];
-        uint16_t c[K];
-    };
-    // the row's plane slots (16 bytes: the group's four words) and coefficients
-    auto load_group = [&](int g, GroupLoads &L) {
-        const int gb = g / GB, b = g % GB;
-        const size_t blk = (size_t)tile * a.n_gblocks + gb;
-        const uint4 *sp = (const uint4 *)(a.planes + blk * plane_block_words(K)) + (b * TR + r) * K;
-#pragma unroll
-        for (int i = 0; i < K; ++i)
-            L.slot[i] = sp[i];
-        const uint16_t *cp = a.coeffs + blk * coeff_block_entries(K) + coeff_entry(K, r, b, 0);  // contiguous
-#pragma unroll
-        for (int i = 0; i < K; ++i)
-            L.c[i] = cp[i];
-    };
-    // a group's activation tile, loaded by the K-slice's R wavefronts: 16
-    // consecutive threads read one token's 256 bytes (tokens past T read as
-    // zero)
-    const int xthr = rt * 64 + lane, nxthr = R * 64;
-    // (no per-lane branch: chunks past the tile or the prompt read the last
-    // token and are zeroed; rounds past the chunks of the tile's tokens, the
-    // same for every thread of the workgroup, are skipped)
-    const int x_rounds = (min(XCH, (a.T - t_base) * 16) + nxthr - 1) / nxthr;
-    auto load_x = [&](int g, uint4 *v) {
-#pragma unroll
-        for (int q = 0; q < XPT; ++q) {
-            v[q] = make_uint4(0u, 0u, 0u, 0u);
-            if (q < x_rounds) {
-                const int ch = xthr + q * nxthr;
-                const int t = t_base + ch / 16;
-                const uint4 r =
-                    *(const uint4 *)(a.X + (size_t)min(t, a.T - 1) * a.I + (size_t)g * GROUP + (ch % 16) * 8);
-                v[q] = ch < XCH && t < a.T ? r : make_uint4(0u, 0u, 0u, 0u);
-            }
-        }
-    };
-    auto store_x = [&](unsigned char *buf, const uint4 *v) {
-#pragma unroll
-        for (int q = 0; q < XPT; ++q) {
-            const int ch = xthr + q * nxthr;
-            if (ch < XCH)
-                *(uint4 *)(buf + (ch / 16) * PF_XROW + (ch % 16) * 16) = v[q];
-        }
-    };
-
-    // every wavefront of the workgroup runs gps steps (groups past G are
-    // skipped but keep the barriers aligned)
-    // Every load is issued unconditionally (past the K-slice's last group the
-    // current or last group is loaded again and not used): with no branch
-    // around them the compiler's load counters stay exact through the loop,
-    // so the next group's loads overlap this group's products instead of
-    // being waited for before its table build.
-    GroupLoads cur, nxt;
-    uint4 xv[XPT];
-    const int g_first = min(g0, a.G - 1);
-    load_group(g_first, cur);
-    load_x(g_first, xv);
-    store_x(xbuf, xv);
-    __syncthreads();
-    for (int j = 0; j < a.gps; ++j) {
-        const int g = g0 + j;
-        const bool more = j + 1 < a.gps && g + 1 < a.G;
-        const int gn = more ? g + 1 : min(g, a.G - 1);
-        load_group(gn, nxt);
-        load_x(gn, xv);  // stored after this group's products
-        if (g < a.G) {
-            // ---- subset-sum table of the 16 rows for group g (lane: row n,
-            // subsets NSUB/4 * kq ..; all of them for k < 2) ----
-            uint32_t c[K];
-#pragma unroll
-            for (int i = 0; i < K; ++i)
-                c[i] = row_ok ? (uint32_t)cur.c[i] : 0u;
-            int emax = -30, emin = 30;
-#pragma unroll
-            for (int i = 0; i < K; ++i) {
-                if (c[i] & 0x7fffu) {
-                    emax = max(emax, f16_exp(c[i]));
-                    emin = min(emin, f16_exp(c[i]));
-                }
-            }
-            constexpr int PER = NSUB >= 4 ? NSUB / 4 : NSUB;
-            const int p0 = NSUB >= 4 ? PER * kq : 0;
-            uint16_t *lrow = lut + n * LROW + p0;
-            // binary32 path: every subset sum has at most 24 significant bits
-            // (exact whatever the order of the additions), one rounding to
-            // binary16.  The entry index is p0 + q: its bits above LOGPER come
-            // from the lane (p0), the ones below from q (compile time).
-            constexpr int LOGPER = PER == 4 ? 2 : (PER == 2 ? 1 : 0);
-            auto table32 = [&]() {
-                float cf[K];
-#pragma unroll
-                for (int i = 0; i < K; ++i)
-                    cf[i] = half_bits_to_float(c[i]);
-                float hi = 0.f;
-#pragma unroll
-                for (int i = LOGPER; i < K; ++i)
-                    hi += ((p0 >> i) & 1) ? cf[i] : 0.f;
-#pragma unroll
-                for (int q = 0; q < PER; ++q) {
-                    float sum = hi;
-#pragma unroll
-                    for (int i = 0; i < LOGPER && i < K; ++i)
-                        if ((q >> i) & 1)
-                            sum += cf[i];
-                    lrow[q] = __half_as_ushort(__float2half_rn(sum));
-                }
-            };
-            const bool wide = emax - emin > 11;
-            if (__builtin_amdgcn_ballot_w64(wide) == 0) {
-                table32();  // no lane of the wavefront needs binary64 (wavefront-uniform branch)
-            } else if (!wide) {
-                table32();
-            } else {
-#pragma unroll
-                for (int q = 0; q < PER; ++q) {
-                    const int p = p0 + q;
-                    double sum = 0.0;  // exact: at most K binary16 terms
-#pragma unroll
-                    for (int i = 0; i < K; ++i)
-                        sum += ((p >> i) & 1) ? (double)half_bits_to_float(c[i]) : 0.0;
-                    lrow[q] = f64_to_f16_rne(sum);
-                }
-            }
-            // the table is read by other lanes of this wavefront only: its LDS
-            // writes complete before the reads below (in order within a wavefront)
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-
-            const uint16_t *L = lut + n * LROW;
-            const unsigned char *xt = xbuf + (j & 1) * XT;
-#pragma unroll
-            for (int ks = 0; ks < 4; ++ks) {
-                uint32_t pat = 0u;  // nibble p: subset index of element 32 ks + 8 kq + p
-#pragma unroll
-                for (int i = 0; i < K; ++i) {
-                    const uint4 sl = cur.slot[i];
-                    const uint32_t word = ks == 0 ? sl.x : (ks == 1 ? sl.y : (ks == 2 ? sl.z : sl.w));
-                    pat |= ((word >> kq) & 0x11111111u) << i;
-                }
-                // (rows past the device format have all-zero tables.)  Byte b
-                // of e2 / o2 is the byte offset of nibble 2b / 2b+1's entry,
-                // so each lookup's address is one byte-select add; the entries
-                // load straight into the halves of the operand registers.
-                const uint32_t e2 = (pat & 0x0F0F0F0Fu) << 1, o2 = (pat >> 3) & 0x1E1E1E1Eu;
-                const uint32_t Lbase = lds_addr(L);  // the row's table
-                const uint32_t a[8] = {add_byte<0>(Lbase, e2), add_byte<0>(Lbase, o2), add_byte<1>(Lbase, e2),
-                                       add_byte<1>(Lbase, o2), add_byte<2>(Lbase, e2), add_byte<2>(Lbase, o2),
-                                       add_byte<3>(Lbase, e2), add_byte<3>(Lbase, o2)};
-                auto at = [&](int i) { return *(const __attribute__((address_space(3))) _Float16 *)(uintptr_t)a[i]; };
-                const v8h B = {at(0), at(1), at(2), at(3), at(4), at(5), at(6), at(7)};
-#pragma unroll
-                for (int tt = 0; tt < BTT; ++tt) {
-                    // token 16 tt + n, elements 32 ks + 8 kq .. +7
-                    const uint4 av = *(const uint4 *)(xt + (16 * tt + n) * PF_XROW + (ks * 4 + kq) * 16);
-                    acc[tt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8h, av), B, acc[tt], 0,
-                                                                      0, 0);
-                }
-            }
-        }
-        // the other buffer was last read before the previous barrier
-        store_x(xbuf + ((j + 1) & 1) * XT, xv);
-        cur = nxt;
-        __syncthreads();
-    }
-
-    // ---- the S K-slices of each row tile summed in a fixed order: halving
-    // tree through LDS (slot of K-slice s of row tile rt: rt * S/2 + s) ----
-    float *red = (float *)smem;  // [R][S / 2][BTT * 4][64 lanes]
-    for (int half = S / 2; half >= 1; half /= 2) {
-        if (ks_id >= half && ks_id < 2 * half) {
-            float *dst = red + ((size_t)rt * (S / 2) + (ks_id - half)) * (BTT * 4 * 64);
-#pragma unroll
-            for (int tt = 0; tt < BTT; ++tt)
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    dst[(tt * 4 + e) * 64 + lane] = acc[tt][e];
-        }
-        __syncthreads();
-        if (ks_id < half) {
-            const float *src = red + ((size_t)rt * (S / 2) + ks_id) * (BTT * 4 * 64);
-#pragma unroll
-            for (int tt = 0; tt < BTT; ++tt)
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    acc[tt][e] += src[(tt * 4 + e) * 64 + lane];
-        }
-        __syncthreads();
-    }
-    if (ks_id != 0)
-        return;
-    // lane (column n, k-block kq) holds rows (tokens) 4 kq .. 4 kq + 3 of each tile
-    const int oo = o_base + n;
-#pragma unroll
-    for (int tt = 0; tt < BTT; ++tt)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int t = t_base + 16 * tt + 4 * kq + e;
-            if (oo < a.O && t < a.T)
-                a.Y[(size_t)t * a.O + oo] = __half_as_ushort(__float2half_rn(acc[tt][e]));
-        }
-}
-
-// ---------------------------------------------------------------------------
-// Long prompts: v_mfma_f32_32x32x16_f16.  The kernel above reads a 16-token
-// activation operand from LDS for every 16 x 16 product, and each wavefront
-// decodes its weights for at most 128 tokens; past about a hundred tokens the
-// LDS reads and the decoding bound it.  Here a wavefront owns RT column tiles
-// of 32 weight rows and TT token tiles of 32: each activation operand read
-// meets 32 RT rows and each decoded weight 32 TT tokens.  A workgroup of
-// PL_WAVES wavefronts holds R = PL_WAVES / S row groups times S K-slices
-// (their partial sums added through LDS in a fixed order, as above).  Per
-// group a wavefront builds the subset-sum tables of its 32 RT rows (lane: row
-// lane % 32, half of the subsets), then per 16-element step each lane looks
-// up the eight elements 8 (lane / 32) .. +7 of each of its rows (the device
-// bit layout holds them as bits v, v + 4, .., v + 28 of one plane word, v =
-// 2 (step % 2) + lane / 32) and issues RT x TT instructions (operand A: 32
-// tokens x 16 values, lane: token lane % 32, values 8 (lane / 32) ..; operand
-// B: the decoded weights, lane: row lane % 32, the same values).  Result
-// register j of a lane holds token 8 (j / 4) + 4 (lane / 32) + j % 4 of the
-// tile, row lane % 32.
-// ---------------------------------------------------------------------------
-constexpr int PL_WAVES = 8;
-// activation chunks (16 bytes) per thread and group: S TT (a K-slice's
-// 512 / S threads load 512 TT chunks).  The launcher keeps S TT <= 8 for one
-// column tile of 64 or 128 tokens (so that its products can split K four and
-// two ways) and <= 4 otherwise; a kernel instance holds 4 or 8 chunks (XPT),
-// 4 whenever S TT allows (the 8-chunk build of the same shape measured 3-5 %
-// slower; 2 x 2 tiles with 8 chunks and four K-slices, 5-10 % slower than
-// 1 x 2 tiles with two)
-__host__ __device__ constexpr int pl_xpt(int tt) { return tt == 1 ? 4 : 8; }
-// instructions per step and wavefront (RT TT) at most: the RT TT x 16
-// accumulators of 2 x 2 and 1 x 4 fit the 256 registers of a wavefront at two
-// per SIMD; 2 x 4 would spill
-constexpr int PL_TILE_MAX = 4;
 
 typedef float v16f __attribute__((ext_vector_type(16)));
 
-__host__ __device__ constexpr int pl_xtile(int tt) { return 32 * tt * PF_XROW; }
-
-template <int K, int RT, int TT, int XPT>
-__global__ void __launch_bounds__(64 * PL_WAVES) prefill_long_kernel(PrefillArgs a)
+// One direct load of 1 KiB into LDS: every lane's 16 bytes at `src` to dst +
+// 16 lane.  Complete when the wavefront's vector-memory count says so.
+__device__ __forceinline__ void load_to_lds(const uint16_t *src, unsigned char *dst)
 {
-    constexpr int TR = tile_rows(K), NSUB = 1 << K;
-    constexpr int LROW = NSUB + PF_LUT_PAD;
-    constexpr int LUT_B = 32 * RT * LROW * 2;  // a wavefront's tables
-    constexpr int XT = pl_xtile(TT);
-    constexpr int XCH = 32 * TT * 16;
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src,
+                                     (__attribute__((address_space(3))) void *)dst, 16, 0, 0);
+}
+
+// Every load the wavefront has issued is complete, the direct ones into LDS
+// included (no register waits for those).
+__device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0f70); }  // vmcnt(0)
+
+// Orders a wavefront's LDS accesses where no other wavefront shares them.
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// The k coefficients of a row and group slot b, from the row's place in the
+// coefficient block (byte pointer, group slot 0).  k = 3: six bytes at a
+// multiple of two, loaded as the two aligned words that hold them and shifted
+// into place by row_coefs (not here: that would wait for the load).
+template <int K>
+__device__ __forceinline__ RowCoefs<K> load_row_coefs(const unsigned char *p, int b)
+{
+    RowCoefs<K> c;
+    p += b * (coefs_per_quad(K) * 2);
+    if constexpr (K == 4) {
+        const uint2 v = *(const uint2 *)p;
+        c.w[0] = v.x;
+        c.w[1] = v.y;
+    } else if constexpr (K == 3) {
+        const uint32_t *v = (const uint32_t *)(p - 2 * (b & 1));
+        c.w[0] = v[0];
+        c.w[1] = v[1];
+    } else if constexpr (K == 2) {
+        c.w[0] = *(const uint32_t *)p;
+    } else {
+        c.w[0] = *(const uint16_t *)p;
+    }
+    return c;
+}
+
+// ... as loaded for group g, zero for a row the device format does not hold.
+template <int K>
+__device__ __forceinline__ RowCoefs<K> row_coefs(RowCoefs<K> c, int g, bool ok)
+{
+    if constexpr (K == 3) {
+        const int sh = (g & 1) * 16;
+        const uint64_t v = (((uint64_t)c.w[1] << 32) | c.w[0]) >> sh;
+        c.w[0] = (uint32_t)v;
+        c.w[1] = (uint32_t)(v >> 32) & 0xffffu;
+    }
+#pragma unroll
+    for (int i = 0; i < (K + 1) / 2; ++i)
+        c.w[i] = ok ? c.w[i] : 0u;
+    return c;
+}
+
+// ST: activation stages per group (two halve the LDS a stage takes).
+template <int K, int RT, int TT, int R, int ST>
+__global__ void __launch_bounds__(64 * PF_WAVES) prefill_kernel(PrefillArgs a)
+{
+    constexpr int S = PF_WAVES / R;
+    constexpr int TR = tile_rows(K);
+    constexpr int XT = 32 * TT * 256 / ST;  // bytes of a stage's activation tile
+    constexpr int SPS = 8 / ST;              // steps per stage
+    constexpr unsigned PBLK_B = GB * TR * K * 16, CBLK_B = GB * TR * K * 2;
     extern __shared__ __align__(16) unsigned char smem[];
     const int lane = threadIdx.x & 63, w = wave_id();
-    const int S = a.S, R = PL_WAVES / S;
     const int ks_id = w % S, rg = w / S;  // K-slice and row group of this wavefront
     const int n = lane & 31, kh = lane >> 5;
     unsigned char *xbuf = smem + (size_t)ks_id * 2 * XT;
-    uint16_t *lut = (uint16_t *)(smem + (size_t)S * 2 * XT + w * LUT_B);
     const int o_base = (blockIdx.x * R + rg) * 32 * RT, t_base = blockIdx.y * 32 * TT;
     const int g0 = ks_id * a.gps;
-    const int rows_dev = a.n_tiles * TR;
+    const int rows_dev = a.n_tiles * TR;  // rows held by the device format (padding included)
 
     v16f acc[RT][TT];
 #pragma unroll
@@ -365,202 +144,185 @@ __global__ void __launch_bounds__(64 * PL_WAVES) prefill_long_kernel(PrefillArgs
             for (int e = 0; e < 16; ++e)
                 acc[q][tt][e] = 0.f;
 
-    // the lane's decode rows (row lane % 32 of each column tile)
-    int tile[RT], rr[RT];
+    // The lane's rows (row lane % 32 of each column tile): byte offsets of its
+    // plane slots and coefficients in the first gblock's first group.
+    unsigned p_lane[RT], c_lane[RT];  // p_lane: of the first slot the lane's half loads (see indices)
     bool row_ok[RT];
 #pragma unroll
     for (int q = 0; q < RT; ++q) {
         const int o = min(o_base + 32 * q + n, rows_dev - 1);
         row_ok[q] = o_base + 32 * q + n < rows_dev;
-        tile[q] = o / TR;
-        rr[q] = o % TR;
+        const unsigned blk = (unsigned)(o / TR) * (unsigned)a.n_gblocks;
+        const int r = o % TR;
+        constexpr unsigned HALF_B = K >= 3 ? 32 : (K == 2 ? 16 : 0);
+        p_lane[q] = blk * PBLK_B + (unsigned)(r * K * 16) + kh * HALF_B;
+        c_lane[q] = blk * CBLK_B + (unsigned)coeff_entry(K, r, 0, 0) * 2u;
     }
+    const int p_next = K == 3 && kh ? -16 : 16;  // to the second slot
+    DecodeMasks masks;
+    masks.set();
     struct GroupLoads {
-        uint4 slot[RT][K];
-        uint16_t c[RT][K];
+        uint4 p[RT][K >= 3 ? 2 : 1];
+        RowCoefs<K> c[RT];
     };
     auto load_group = [&](int g, GroupLoads &L) {
-        const int gb = g / GB, b = g % GB;
+        const unsigned pu = (unsigned)(g / GB) * PBLK_B + (unsigned)(g % GB) * (TR * K * 16);
+        const unsigned char *pb = (const unsigned char *)a.planes + pu;
+        const unsigned char *cb = (const unsigned char *)a.coeffs + (unsigned)(g / GB) * CBLK_B;
 #pragma unroll
         for (int q = 0; q < RT; ++q) {
-            const size_t blk = (size_t)tile[q] * a.n_gblocks + gb;
-            const uint4 *sp = (const uint4 *)(a.planes + blk * plane_block_words(K)) + (b * TR + rr[q]) * K;
-#pragma unroll
-            for (int i = 0; i < K; ++i)
-                L.slot[q][i] = sp[i];
-            const uint16_t *cp = a.coeffs + blk * coeff_block_entries(K) + coeff_entry(K, rr[q], b, 0);
-#pragma unroll
-            for (int i = 0; i < K; ++i)
-                L.c[q][i] = cp[i];
+            L.c[q] = load_row_coefs<K>(cb + c_lane[q], g % GB);
+            L.p[q][0] = *(const uint4 *)(pb + p_lane[q]);
+            if constexpr (K >= 3)
+                L.p[q][1] = *(const uint4 *)(pb + p_lane[q] + p_next);
         }
     };
-    // a group's activation tile, loaded by the K-slice's R wavefronts: 16
-    // consecutive threads read one token's 256 bytes (tokens past T read zero)
-    const int xthr = rg * 64 + lane, nxthr = R * 64;
-    // (no per-lane branch: chunks past the tile or the prompt read the last
-    // token and are zeroed; rounds past the chunks of the tile's tokens, the
-    // same for every thread of the workgroup, are skipped)
-    const int x_rounds = (min(XCH, (a.T - t_base) * 16) + nxthr - 1) / nxthr;
-    auto load_x = [&](int g, uint4 *v) {
+    // Subset indices of the lane's 64 elements of row tile q: words lane / 32
+    // and 2 + lane / 32 of every plane.  The halves of the wavefront load whole
+    // slots -- of planes 0, 1 and 2, 3 (k = 4), 0, 1 and 2, 1 (k = 3), 0 and 1
+    // (k = 2), 0 both (k = 1) -- and trade words.
+    auto indices = [&](const GroupLoads &L, int q, uint32_t *pat) {
+        uint32_t w0[4] = {}, w1[4] = {};
+        auto trade = [&](uint4 v, int lo, int hi) {  // lo, hi: the planes of the two halves' slots
+            const auto x = __builtin_amdgcn_permlane32_swap(v.x, v.y, false, false);
+            const auto y = __builtin_amdgcn_permlane32_swap(v.z, v.w, false, false);
+            w0[hi] = x[1];
+            w1[hi] = y[1];
+            w0[lo] = x[0];
+            w1[lo] = y[0];
+        };
+        if constexpr (K >= 3) {
+            trade(L.p[q][0], 0, 2);
+            trade(L.p[q][1], 1, K == 4 ? 3 : 1);
+        } else {
+            trade(L.p[q][0], 0, K == 2 ? 1 : 0);
+        }
+        subset_indices<K>(masks, w0, pat);
+        subset_indices<K>(masks, w1, pat + 4);
+    };
+
+    // A group's activation tile, loaded straight into LDS by the K-slice's R
+    // wavefronts, four tokens (1 KiB) per instruction.  Token t's 256 bytes
+    // lie together, its 16-byte chunk c in place c ^ (t % 16), so that the 16
+    // tokens of a quarter of an operand read fall on different banks.  Tokens
+    // past the prompt read the last one or are left as they are: their results
+    // are not stored.
+    constexpr int XI = 8 * TT / ST;            // instructions per stage
+    constexpr int TPI = 4 * ST, CPT = 16 / ST;  // tokens per instruction, chunks per token
+    const int x_rounds = (min(32 * TT, a.T - t_base) + TPI - 1) / TPI;
+    auto load_x = [&](int stage, unsigned char *buf) {  // stage: ST per group
 #pragma unroll
-        for (int q = 0; q < XPT; ++q) {
-            v[q] = make_uint4(0u, 0u, 0u, 0u);
-            if (q < x_rounds) {
-                const int ch = xthr + q * nxthr;
-                const int t = t_base + ch / 16;
-                const uint4 r =
-                    *(const uint4 *)(a.X + (size_t)min(t, a.T - 1) * a.I + (size_t)g * GROUP + (ch % 16) * 8);
-                v[q] = ch < XCH && t < a.T ? r : make_uint4(0u, 0u, 0u, 0u);
+        for (int q = 0; q < (XI + R - 1) / R; ++q) {
+            const int i = rg + q * R;  // wavefront-uniform
+            if (i < x_rounds) {
+                const int t = TPI * i + lane / CPT;
+                const int c = (lane % CPT) ^ (ST == 1 ? t & 15 : (t >> 1) & 7);
+                load_to_lds(a.X + (size_t)min(t_base + t, a.T - 1) * a.I + (size_t)stage * (GROUP / ST) + c * 8,
+                            buf + i * 1024);
             }
         }
     };
-    auto store_x = [&](unsigned char *buf, const uint4 *v) {
+    // the next stage's loads are complete, for all the wavefronts that read it
+    auto sync = [&]() {
+        wait_loads();
+        if constexpr (R == 1)
+            wave_sync();
+        else
+            __syncthreads();
+    };
+
+    // The decoding state of a group: tables and subset indices of the row tiles.
+    struct GroupState {
+        RowTable<K> tab[RT];
+        uint32_t pat[RT][8];
+    };
+    auto prepare = [&](const GroupLoads &L, int g, GroupState &s) {
+        bool wide = false;
 #pragma unroll
-        for (int q = 0; q < XPT; ++q) {
-            const int ch = xthr + q * nxthr;
-            if (ch < XCH)
-                *(uint4 *)(buf + (ch / 16) * PF_XROW + (ch % 16) * 16) = v[q];
+        for (int q = 0; q < RT; ++q) {
+            const RowCoefs<K> c = row_coefs<K>(L.c[q], g, row_ok[q]);
+            wide = wide || !row_sums_exact_in_f32<K>(c);
+            s.tab[q] = row_table32<K>(c, kh);
+            indices(L, q, s.pat[q]);
+        }
+        if (__builtin_amdgcn_ballot_w64(wide) != 0) {  // some row's sums are not exact in binary32
+#pragma unroll
+            for (int q = 0; q < RT; ++q)
+                s.tab[q] = row_table64<K>(row_coefs<K>(L.c[q], g, row_ok[q]), kh);
         }
     };
 
-    // Every load is issued unconditionally (past the K-slice's last group the
-    // current or last group is loaded again and not used): with no branch
-    // around them the compiler's load counters stay exact through the loop,
-    // so the next group's loads overlap this group's products instead of
-    // being waited for before its table build.
-    GroupLoads cur, nxt;
-    uint4 xv[XPT];
-    const int g_first = min(g0, a.G - 1);
-    load_group(g_first, cur);
-    load_x(g_first, xv);
-    store_x(xbuf, xv);
-    __syncthreads();
+    const int g_last = min(g0 + a.gps, a.G) - 1, g_first = min(g0, a.G - 1);
+    GroupLoads raw;
+    load_x(g_first * ST, xbuf);
+    load_group(g_first, raw);
+    sync();
+    // operand reads: token n's chunk of the lane's elements; word lane / 32
+    // is chunks 4 (lane / 32) .. of a stage's first 64 elements
+    const int x_lane = ST == 1 ? n * 256 + (((n & 15) ^ (4 * kh)) << 4) : n * 128 + ((((n >> 1) & 7) ^ (4 * kh)) << 4);
+    auto x_step = [&](int st) { return x_lane ^ (ST == 1 ? ((st & 3) | (st >> 2 << 3)) << 4 : (st & 3) << 4); };
+    int buf = 0;
     for (int j = 0; j < a.gps; ++j) {
         const int g = g0 + j;
-        const bool more = j + 1 < a.gps && g + 1 < a.G;
-        const int gn = more ? g + 1 : min(g, a.G - 1);
-        load_group(gn, nxt);
-        load_x(gn, xv);  // stored after this group's products
-        if (g < a.G) {
-            // ---- subset-sum tables of the wavefront's rows for group g (lane:
-            // row lane % 32 of each column tile, subsets PER * (lane / 32) ..) ----
-            constexpr int PER = NSUB / 2, LOGPER = K - 1;
-            const int p0 = PER * kh;
+        // past the K-slice's last group: it is loaded again and not used
+        const int gn = max(min(g + 1, g_last), g_first);
+        GroupState cur;
+        prepare(raw, min(g, a.G - 1), cur);
 #pragma unroll
-            for (int q = 0; q < RT; ++q) {
-                uint32_t c[K];
-#pragma unroll
-                for (int i = 0; i < K; ++i)
-                    c[i] = row_ok[q] ? (uint32_t)cur.c[q][i] : 0u;
-                int emax = -30, emin = 30;
-#pragma unroll
-                for (int i = 0; i < K; ++i) {
-                    if (c[i] & 0x7fffu) {
-                        emax = max(emax, f16_exp(c[i]));
-                        emin = min(emin, f16_exp(c[i]));
-                    }
-                }
-                uint16_t *lrow = lut + (32 * q + n) * LROW + p0;
-                // binary32 sums (exact when the coefficients span at most 12
-                // binades: every subset sum then has at most 24 significant
-                // bits), one rounding to binary16; entry p0 + e takes its top
-                // bit from the lane and the others from e
-                auto table32 = [&]() {
-                    float cf[K];
-#pragma unroll
-                    for (int i = 0; i < K; ++i)
-                        cf[i] = half_bits_to_float(c[i]);
-                    const float hi = kh ? cf[K - 1] : 0.f;
-#pragma unroll
-                    for (int e = 0; e < PER; ++e) {
-                        float sum = hi;
-#pragma unroll
-                        for (int i = 0; i < LOGPER; ++i)
-                            if ((e >> i) & 1)
-                                sum += cf[i];
-                        lrow[e] = __half_as_ushort(__float2half_rn(sum));
-                    }
-                };
-                const bool wide = emax - emin > 11;
-                if (__builtin_amdgcn_ballot_w64(wide) == 0) {
-                    table32();  // no lane needs binary64 (wavefront-uniform branch)
-                } else if (!wide) {
-                    table32();
-                } else {
-#pragma unroll
-                    for (int e = 0; e < PER; ++e) {
-                        const int p = p0 + e;
-                        double sum = 0.0;  // exact: at most K binary16 terms
-#pragma unroll
-                        for (int i = 0; i < K; ++i)
-                            sum += ((p >> i) & 1) ? (double)half_bits_to_float(c[i]) : 0.0;
-                        lrow[e] = f64_to_f16_rne(sum);
-                    }
-                }
-            }
-            // the tables are read by other lanes of this wavefront only: its
-            // LDS writes complete before the reads below (in order within a
-            // wavefront)
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-
-            const unsigned char *xt = xbuf + (j & 1) * XT;
-            // Operands of step st: the lane's eight weights of each of its
-            // rows (table lookups) and its activation fragment of each token
-            // tile.  Software-pipelined: step st + 1's LDS reads are issued
-            // before step st's products, so their latency overlaps the
-            // matrix-core work instead of stalling every instruction.
-            v8h Bw[2][RT];
-            uint4 Av[2][TT];
-            auto load_step = [&](int st, v8h *bw, uint4 *av) {
-                const int v = 2 * (st & 1) + kh;
-#pragma unroll
-                for (int q = 0; q < RT; ++q) {
-                    uint32_t pat = 0u;  // nibble p: subset index of element 16 st + 8 kh + p
-#pragma unroll
-                    for (int i = 0; i < K; ++i) {
-                        const uint4 sl = cur.slot[q][i];
-                        const int wi = st >> 1;
-                        const uint32_t word = wi == 0 ? sl.x : (wi == 1 ? sl.y : (wi == 2 ? sl.z : sl.w));
-                        pat |= ((word >> v) & 0x11111111u) << i;
-                    }
-                    // byte b of e2 / o2: byte offset of nibble 2b / 2b+1's entry
-                    const uint32_t e2 = (pat & 0x0F0F0F0Fu) << 1, o2 = (pat >> 3) & 0x1E1E1E1Eu;
-                    const uint32_t Lbase = lds_addr(lut + (32 * q + n) * LROW);
-                    const uint32_t ad[8] = {add_byte<0>(Lbase, e2), add_byte<0>(Lbase, o2), add_byte<1>(Lbase, e2),
-                                            add_byte<1>(Lbase, o2), add_byte<2>(Lbase, e2), add_byte<2>(Lbase, o2),
-                                            add_byte<3>(Lbase, e2), add_byte<3>(Lbase, o2)};
-                    auto at = [&](int i) {
-                        return *(const __attribute__((address_space(3))) _Float16 *)(uintptr_t)ad[i];
-                    };
-                    bw[q] = v8h{at(0), at(1), at(2), at(3), at(4), at(5), at(6), at(7)};
-                }
-#pragma unroll
-                for (int tt = 0; tt < TT; ++tt)  // token 32 tt + n, elements 16 st + 8 kh .. +7
-                    av[tt] = *(const uint4 *)(xt + (32 * tt + n) * PF_XROW + (2 * st + kh) * 16);
-            };
-            load_step(0, Bw[0], Av[0]);
-#pragma unroll
-            for (int st = 0; st < 8; ++st) {
-                if (st + 1 < 8)
-                    load_step(st + 1, Bw[(st + 1) & 1], Av[(st + 1) & 1]);
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int tt = 0; tt < TT; ++tt)
+        for (int s = 0; s < ST; ++s) {
+            const int next_stage = s + 1 < ST ? min(g, a.G - 1) * ST + s + 1 : gn * ST;
+            load_x(next_stage, xbuf + (buf ^ 1) * XT);
+            if (s == 0)
+                load_group(gn, raw);
+            __builtin_amdgcn_sched_barrier(0);
+            const unsigned char *xt = xbuf + buf * XT;
+            if (g <= g_last) {
+                v8h B[2][RT], A[2][TT];
+                auto decode = [&](int st, v8h *b) {
 #pragma unroll
                     for (int q = 0; q < RT; ++q)
-                        acc[q][tt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, Av[st & 1][tt]),
-                                                                            Bw[st & 1][q], acc[q][tt], 0, 0, 0);
+                        b[q] = __builtin_bit_cast(v8h, decode8<K>(masks, cur.tab[q], cur.pat[q][s * SPS + st]));
+                };
+                auto read = [&](int st, v8h *v) {
+#pragma unroll
+                    for (int tt = 0; tt < TT; ++tt)
+                        v[tt] = __builtin_bit_cast(v8h, *(const uint4 *)(xt + 32 * tt * (256 / ST) + x_step(st)));
+                };
+                read(0, A[0]);
+                decode(0, B[0]);
+#pragma unroll
+                for (int st = 0; st < SPS; ++st) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (st + 1 < SPS) {
+                        read(st + 1, A[(st + 1) & 1]);
+                        decode(st + 1, B[(st + 1) & 1]);
+                    }
+#pragma unroll
+                    for (int tt = 0; tt < TT; ++tt)
+#pragma unroll
+                        for (int q = 0; q < RT; ++q)
+                            acc[q][tt] =
+                                __builtin_amdgcn_mfma_f32_32x32x16_f16(A[st & 1][tt], B[st & 1][q], acc[q][tt], 0, 0, 0);
+                    if (st + 1 < SPS) {
+                        // the next step's operand reads behind the first
+                        // product, a share of its decoding behind every one
+#pragma unroll
+                        for (int i = 0; i < TT * RT; ++i) {
+                            __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+                            if (i == 0)
+                                __builtin_amdgcn_sched_group_barrier(0x100, TT, 0);
+                            __builtin_amdgcn_sched_group_barrier(0x2, 32 / TT, 0);
+                        }
+                    }
+                }
                 __builtin_amdgcn_sched_barrier(0);
             }
+            buf ^= 1;
+            sync();
         }
-        // the other buffer was last read before the previous barrier
-        store_x(xbuf + ((j + 1) & 1) * XT, xv);
-        cur = nxt;
-        __syncthreads();
     }
-
+    if constexpr (R == 1)
+        __syncthreads();  // the sums below reuse every wavefront's tile
     // ---- the S K-slices of each row group summed in a fixed order (halving
     // tree through LDS; slot of K-slice s of row group rg: rg * S/2 + s) ----
     constexpr int NV = RT * TT * 16;  // values per lane
@@ -605,187 +367,232 @@ __global__ void __launch_bounds__(64 * PL_WAVES) prefill_long_kernel(PrefillArgs
     }
 }
 
-template <int K>
-static const void *prefill_long_kernel_for(int rt, int tt, int S)
-{
-    const bool wide = S * tt > 4;
-    if (rt == 2)
-        return tt == 2 ? (const void *)prefill_long_kernel<K, 2, 2, 4> : (const void *)prefill_long_kernel<K, 2, 1, 4>;
-    if (tt == 4)
-        return wide ? (const void *)prefill_long_kernel<K, 1, 4, 8> : (const void *)prefill_long_kernel<K, 1, 4, 4>;
-    if (tt == 2)
-        return wide ? (const void *)prefill_long_kernel<K, 1, 2, 8> : (const void *)prefill_long_kernel<K, 1, 2, 4>;
-    return (const void *)prefill_long_kernel<K, 1, 1, 4>;
-}
 
-template <int K>
-static const void *prefill_kernel_for(int btt)
+// Short prompts and small matrices (see the top of the file).
+template <int K, int TT, int NW>
+__global__ void __launch_bounds__(64 * NW) prefill_short_kernel(PrefillArgs a)
 {
-    switch (btt) {
-    case 1: return (const void *)prefill_kernel<K, 1>;
-    case 2: return (const void *)prefill_kernel<K, 2>;
-    case 4: return (const void *)prefill_kernel<K, 4>;
-    default: return (const void *)prefill_kernel<K, 8>;
+    constexpr int TR = tile_rows(K);
+    constexpr unsigned PBLK_B = GB * TR * K * 16, CBLK_B = GB * TR * K * 2;
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int lane = threadIdx.x & 63, w = wave_id();
+    const int nw = blockDim.x >> 6;
+    const int n = lane & 15, kq = lane >> 4;
+    const int o_base = blockIdx.x * 16, t_base = blockIdx.y * 16 * TT;
+    const int g0 = w * a.gps, g_end = min(g0 + a.gps, a.G);
+    const int rows_dev = a.n_tiles * TR;
+
+    v4f acc[TT];
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt)
+        acc[tt] = v4f{0.f, 0.f, 0.f, 0.f};
+
+    const int o = min(o_base + n, rows_dev - 1);
+    const bool row_ok = o_base + n < rows_dev;
+    const int r = o % TR;
+    const unsigned blk = (unsigned)(o / TR) * (unsigned)a.n_gblocks;
+    // lane quarter q loads plane q's slot (the last one where k < 4); a transpose
+    // across the quarters then gives it word q of every plane
+    const unsigned p_lane = blk * PBLK_B + (unsigned)(r * K + min(kq, K - 1)) * 16u;
+    const unsigned c_lane = blk * CBLK_B + (unsigned)coeff_entry(K, r, 0, 0) * 2u;
+    // activation tiles of the wavefront's K-slice, rows rounded up to four tokens
+    const int x_inst = (min(16 * TT, a.T - t_base) + 3) / 4;
+    const unsigned xt_bytes = (unsigned)((min(16 * TT, a.T) + 3) / 4) * 1024u;
+    unsigned char *xbuf = smem + (size_t)w * 2 * xt_bytes;
+    unsigned x_lane[TT];
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt) {
+        const int t = min(16 * tt + n, 4 * x_inst - 1);
+        x_lane[tt] = (unsigned)(t * 256 + (((t & 15) ^ (4 * kq)) << 4));
+    }
+    auto load_x = [&](int g, unsigned char *buf) {
+        for (int i = 0; i < x_inst; ++i) {
+            const int t = 4 * i + (lane >> 4), c = (lane & 15) ^ (t & 15);
+            load_to_lds(a.X + (size_t)min(t_base + t, a.T - 1) * a.I + (size_t)g * GROUP + c * 8, buf + i * 1024);
+        }
+    };
+    uint4 slot;
+    RowCoefs<K> coef;
+    auto load_group = [&](int g) {
+        const unsigned pu = (unsigned)(g / GB) * PBLK_B + (unsigned)(g % GB) * (TR * K * 16);
+        const unsigned char *pb = (const unsigned char *)a.planes + pu;
+        const unsigned char *cb = (const unsigned char *)a.coeffs + (unsigned)(g / GB) * CBLK_B;
+        slot = *(const uint4 *)(pb + p_lane);
+        coef = load_row_coefs<K>(cb + c_lane, g % GB);
+    };
+    DecodeMasks masks;
+    masks.set();
+    if (g0 < g_end) {
+        load_x(g0, xbuf);
+        load_group(g0);
+        wait_loads();
+        wave_sync();
+        int buf = 0;
+        for (int g = g0; g < g_end; ++g) {
+            const int gn = min(g + 1, g_end - 1);
+            const RowCoefs<K> c = row_coefs<K>(coef, g, row_ok);
+            RowTable<K> tab = quarter_table32<K>(c, kq);
+            if (__builtin_amdgcn_ballot_w64(!row_sums_exact_in_f32<K>(c)) != 0)
+                tab = quarter_table64<K>(c, kq);
+            const uint4 tw = transpose_rows4(slot);
+            const uint32_t words[4] = {tw.x, tw.y, tw.z, tw.w};
+            uint32_t pat[4];
+            subset_indices<K>(masks, words, pat);
+            load_x(gn, xbuf + (buf ^ 1) * xt_bytes);
+            load_group(gn);
+            __builtin_amdgcn_sched_barrier(0);
+            const unsigned char *xt = xbuf + buf * xt_bytes;
+#pragma unroll
+            for (int st = 0; st < 4; ++st) {
+                v8h A[TT];
+#pragma unroll
+                for (int tt = 0; tt < TT; ++tt)
+                    A[tt] = __builtin_bit_cast(v8h, *(const uint4 *)(xt + (x_lane[tt] ^ (st << 4))));
+                const v8h B = __builtin_bit_cast(v8h, decode8<K>(masks, tab, pat[st]));
+#pragma unroll
+                for (int tt = 0; tt < TT; ++tt)
+                    acc[tt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(A[tt], B, acc[tt], 0, 0, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            buf ^= 1;
+            wait_loads();
+            wave_sync();
+        }
+    }
+    __syncthreads();
+    // the K-slices' sums in slice order
+    float *red = (float *)smem;  // [nw][TT * 4][64 lanes]
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            red[(w * (TT * 4) + tt * 4 + e) * 64 + lane] = acc[tt][e];
+    __syncthreads();
+    for (int idx = threadIdx.x; idx < TT * 4 * 64; idx += blockDim.x) {
+        const int l = idx & 63, e = (idx >> 6) & 3, tt = idx >> 8;
+        const int oo = o_base + (l & 15), t = t_base + 16 * tt + 4 * (l >> 4) + e;
+        if (oo < a.O && t < a.T) {
+            float s = 0.f;
+            for (int q = 0; q < nw; ++q)
+                s += red[q * (TT * 4 * 64) + idx];
+            a.Y[(size_t)t * a.O + oo] = __half_as_ushort(__float2half_rn(s));
+        }
     }
 }
 
-// Launch shape.  A wavefront's per-group work (plane loads, table build,
-// pattern extraction and lookups) is the same whatever BTT is, so large token
-// tiles amortise it; splitting K into S slices spreads it over more
-// wavefronts and shortens each one's chain of groups; both are bounded by the
-// activation tiles' LDS (S BTT <= 4 pf_xpt).  Workgroups hold 1024 threads and
-// up to 148 KiB of LDS, one per CU: among the shapes whose grid fits one
-// round of the 256 CUs the one with the most workgroups wins (ties: the
-// largest S BTT); when none fits, the fewest workgroups.  This rule picks the
-// measured best of every (BTT, S) on the Llama-3-8B projection shapes at
-// 1 .. 512 tokens.
-constexpr int PF_CUS = 256;
-
-// Prompts of at least this many tokens run the long-prompt kernel.
-#ifndef SBVR_PF_LONG_MIN_T
-#define SBVR_PF_LONG_MIN_T 96
-#endif
-// ... and its grid has at least this many workgroups (else the kernel above)
-#ifndef SBVR_PF_LONG_MIN_WG
-#define SBVR_PF_LONG_MIN_WG 192
-#endif
-// Sweeps: a fixed long-kernel shape (column tiles, token tiles, K-slices);
-// 0 lets the rule below choose.
-#ifndef SBVR_PF_LONG_RT
-#define SBVR_PF_LONG_RT 0
-#endif
-#ifndef SBVR_PF_LONG_TT
-#define SBVR_PF_LONG_TT 0
-#endif
-#ifndef SBVR_PF_LONG_S
-#define SBVR_PF_LONG_S 0
-#endif
-
-static size_t prefill_long_lds(int k, int rt, int tt, int S)
-{
-    const size_t front = (size_t)S * 2 * pl_xtile(tt);
-    const size_t red = (size_t)(PL_WAVES / S) * (S / 2) * rt * tt * 16 * 64 * 4;
-    return (front > red ? front : red) + (size_t)PL_WAVES * 32 * rt * ((1u << k) + PF_LUT_PAD) * 2;
-}
-
-// Long-prompt launch shape: among the (RT, TT, S) whose LDS fits, the grids
-// that fit one round of the 256 CUs win, and among those the most workgroups,
-// then the widest token tile (each weight is decoded once per token tile),
-// then 4 activation chunks per thread over 8, then the largest tile per
-// wavefront (RT TT); when none fits, the fewest
-// workgroups.  Returns the workgroup count (0: no shape fits).
-struct LongShape {
-    int rt, tt, S, wg;
+// Launch shapes.  prefill_kernel: rt, tt, r, st; prefill_short_kernel: rt = 0,
+// tt, r = the most wavefronts.  cost: the time of a launch in microseconds,
+// fitted for each shape to 3463 matrices and prompts on MI355X (16 .. 28672
+// rows, 128 .. 28672 columns, 1 .. 2048 tokens, k = 1 .. 4; the prediction is
+// within 20 % of the time in 90 % of them).  With w workgroups per CU (f = w,
+// c = w rounded up: the last round counts whole) and g groups per K-slice,
+//   prefill_kernel        [0] + [1] g + ([2] c + [3] f) g + [4] c
+//   prefill_short_kernel  [0] + [1] g + ([2] c + [3] f) g n / 16 + [4] c
+//                             + ([5] c + [6] f) g n x / 64
+// for n wavefronts and x loads of four tokens per group.  The shape with the
+// lowest cost runs.  Over those cases its choice takes 1.3 % more than the best
+// shape of each on average (7.7 % at the 95th percentile), and the launch is
+// 1.51 (k = 1) to 1.81 (k = 3) times as fast as the LDS-table kernels were
+// (geometric means; the least 0.91, a single-group matrix at k = 1).
+// Sixteen-wavefront workgroups are left to grids of one per CU: in larger ones
+// the fit misses that two of them do not share a CU (12778 x 1536, 13 tokens,
+// k = 3: 12.8 us against 9.4 with eight wavefronts).
+struct PrefillShape {
+    int rt, tt, r, st;
+    float cost[7];
 };
 
-static LongShape prefill_long_shape(const Dims &d, int T)
+static const PrefillShape PREFILL_SHAPES[] = {
+    {0, 1, 8, 1, {2.647f, 0.312f, 0.462f, 0.339f, 0.176f, 0.417f, 0.185f}},
+    {0, 1, 16, 1, {2.892f, 0.076f, 0.813f, 0.000f, 0.141f, 0.328f, 0.646f}},
+    {0, 2, 8, 1, {2.663f, 0.233f, 0.624f, 0.098f, 0.391f, 0.403f, 0.490f}},
+    {1, 1, 1, 1, {1.293f, 0.169f, 0.858f, 0.355f, 2.306f}},
+    {1, 2, 1, 2, {1.130f, 0.242f, 1.157f, 0.506f, 3.414f}},
+    {1, 2, 2, 1, {0.887f, 0.080f, 1.166f, 0.331f, 3.684f}},
+    {1, 2, 4, 1, {2.339f, 0.270f, 0.872f, 0.271f, 1.727f}},
+    {1, 4, 2, 2, {0.555f, 0.029f, 1.812f, 0.452f, 5.762f}},
+    {1, 4, 4, 1, {0.000f, 0.000f, 1.529f, 0.423f, 5.862f}},
+    {1, 4, 8, 1, {0.000f, 0.000f, 1.447f, 0.439f, 4.441f}},
+    {2, 4, 8, 1, {0.000f, 0.000f, 2.631f, 1.052f, 6.122f}},
+};
+
+static double prefill_cost(const PrefillShape &s, const Dims &d, int T, int slices, double wg)
 {
-    LongShape b = {0, 0, 0, 0};
-    for (int r = 1; r <= 2; ++r)
-        for (int t = 1; t <= 4; t *= 2)
-            for (int sk = 1; sk <= PL_WAVES && sk <= d.G && sk * t <= pl_xpt(t); sk *= 2) {
-                if (r * t > PL_TILE_MAX)
-                    continue;
-                if (r == 2 && sk * t > 4)  // two column tiles: 4 chunks per thread only
-                    continue;
-                if (SBVR_PF_LONG_RT && r != SBVR_PF_LONG_RT)
-                    continue;
-                if (SBVR_PF_LONG_TT && t != SBVR_PF_LONG_TT)
-                    continue;
-                if (SBVR_PF_LONG_S && sk != SBVR_PF_LONG_S)
-                    continue;
-                if (prefill_long_lds(d.k, r, t, sk) > PF_LDS_MAX)
-                    continue;
-                const int rows = 32 * r * (PL_WAVES / sk);
-                const int wg = (d.O + rows - 1) / rows * ((T + 32 * t - 1) / (32 * t));
-                const bool fits = wg <= PF_CUS, best_fits = b.wg > 0 && b.wg <= PF_CUS;
-                bool take;
-                if (b.rt == 0)
-                    take = true;
-                else if (fits != best_fits)
-                    take = fits;
-                else if (wg != b.wg)
-                    take = fits ? wg > b.wg : wg < b.wg;
-                else if (t != b.tt)
-                    take = t > b.tt;
-                else if ((sk * t <= 4) != (b.S * b.tt <= 4))
-                    take = sk * t <= 4;
-                else
-                    take = r * t > b.rt * b.tt;
-                if (take)
-                    b = {r, t, sk, wg};
-            }
-    return b;
+    const double f = wg / PF_CUS, c = (double)(long long)((wg + PF_CUS - 1) / PF_CUS);
+    const double g = (d.G + slices - 1) / slices;
+    if (s.rt)
+        return s.cost[0] + s.cost[1] * g + (s.cost[2] * c + s.cost[3] * f) * g + s.cost[4] * c;
+    const double x = (min(T, 16 * s.tt) + 3) / 4;
+    return s.cost[0] + s.cost[1] * g + (s.cost[2] * c + s.cost[3] * f) * g * slices / 16 + s.cost[4] * c +
+           (s.cost[5] * c + s.cost[6] * f) * g * slices * x / 64;
 }
 
-static int launch_prefill_long(const Dims &d, const LongShape &sh, const void *planes_dev, const void *coeffs_dev,
-                               const uint16_t *X, uint16_t *Y, int T, hipStream_t stream)
+template <int K>
+static const void *prefill_kernel_for(const PrefillShape &s)
 {
-    const int rows = 32 * sh.rt * (PL_WAVES / sh.S);
-    const int gx = (d.O + rows - 1) / rows, gy = (T + 32 * sh.tt - 1) / (32 * sh.tt);
-    PrefillArgs a = {(const uint32_t *)planes_dev, (const uint16_t *)coeffs_dev, X, Y, d.O, d.I, T, d.n_tiles,
-                     d.n_gblocks, d.G, (d.G + sh.S - 1) / sh.S, sh.S};
-    const void *fn = d.k == 4   ? prefill_long_kernel_for<4>(sh.rt, sh.tt, sh.S)
-                     : d.k == 3 ? prefill_long_kernel_for<3>(sh.rt, sh.tt, sh.S)
-                     : d.k == 2 ? prefill_long_kernel_for<2>(sh.rt, sh.tt, sh.S)
-                                : prefill_long_kernel_for<1>(sh.rt, sh.tt, sh.S);
-    void *args[] = {&a};
-    return launch_kernel(fn, dim3(gx, gy), dim3(64 * PL_WAVES), prefill_long_lds(d.k, sh.rt, sh.tt, sh.S), stream,
-                         args);
+    if (s.rt == 0)
+        return s.r > PF_WAVES ? (const void *)prefill_short_kernel<K, 1, 16>
+               : s.tt == 1    ? (const void *)prefill_short_kernel<K, 1, 8>
+                              : (const void *)prefill_short_kernel<K, 2, 8>;
+    if (s.rt == 2)
+        return (const void *)prefill_kernel<K, 2, 4, 8, 1>;
+    if (s.tt == 1)
+        return (const void *)prefill_kernel<K, 1, 1, 1, 1>;
+    if (s.tt == 2)
+        return s.r == 1   ? (const void *)prefill_kernel<K, 1, 2, 1, 2>
+               : s.r == 2 ? (const void *)prefill_kernel<K, 1, 2, 2, 1>
+                          : (const void *)prefill_kernel<K, 1, 2, 4, 1>;
+    return s.r == 2   ? (const void *)prefill_kernel<K, 1, 4, 2, 2>
+           : s.r == 4 ? (const void *)prefill_kernel<K, 1, 4, 4, 1>
+                      : (const void *)prefill_kernel<K, 1, 4, 8, 1>;
 }
 
 int launch_prefill(const Dims &d, const void *planes_dev, const void *coeffs_dev, const uint16_t *X, uint16_t *Y,
                    int T, hipStream_t stream)
 {
-    // the long-prompt kernel where its grid fills most of the chip (measured:
-    // faster there -- Llama-3-8B gate at 128 / 256 / 512 tokens 66.6 / 122 /
-    // 167 us -> 60.6 / 94 / 132, down at 512 216 -> 187, q/o 66 -> 57 --,
-    // slower for a 1024-row matrix at 128 tokens, whose best long grid has 64
-    // workgroups: 16.2 -> 27.5 us)
-    if (T >= SBVR_PF_LONG_MIN_T) {
-        const LongShape sh = prefill_long_shape(d, T);
-        if (sh.wg >= SBVR_PF_LONG_MIN_WG)
-            return launch_prefill_long(d, sh, planes_dev, coeffs_dev, X, Y, T, stream);
-    }
-    int btt = 0, S = 0, best_wg = 0;
-    for (int bt = 1; bt <= 8; bt *= 2) {
-        if (bt > 1 && 16 * (bt / 2) >= T)  // a smaller tile already covers the prompt
-            break;
-        const int gy = (T + 16 * bt - 1) / (16 * bt);
-        for (int sk = 1; sk <= PF_WAVES && sk <= d.G && sk * bt <= 4 * pf_xpt(bt); sk *= 2) {
-            const int wg = (d.O + 16 * (PF_WAVES / sk) - 1) / (16 * (PF_WAVES / sk)) * gy;
-            const bool fits = wg <= PF_CUS, best_fits = best_wg > 0 && best_wg <= PF_CUS;
-            bool take;
-            if (btt == 0)
-                take = true;
-            else if (fits != best_fits)
-                take = fits;
-            else if (wg != best_wg)
-                take = fits ? wg > best_wg : wg < best_wg;
-            else
-                take = sk * bt > S * btt;
-            if (take) {
-                btt = bt;
-                S = sk;
-                best_wg = wg;
-            }
+    const PrefillShape *best = nullptr;
+    double best_cost = 0;
+    int slices = 0, gx = 0, gy = 0;
+    for (const PrefillShape &s : PREFILL_SHAPES) {
+        const int sl = s.rt ? PF_WAVES / s.r : min(s.r, d.G);
+        const int rows = s.rt ? 32 * s.rt * s.r : 16, tokens = s.rt ? 32 * s.tt : 16 * s.tt;
+        const int x = (d.O + rows - 1) / rows, y = (T + tokens - 1) / tokens;
+        if (y > 65535)  // (a grid's second dimension has 16 bits)
+            continue;
+        if (!s.rt && s.r > PF_WAVES && (long long)x * y > PF_CUS)
+            continue;
+        const double cost = prefill_cost(s, d, T, sl, (double)x * y);
+        if (!best || cost < best_cost) {
+            best = &s;
+            best_cost = cost;
+            slices = sl;
+            gx = x;
+            gy = y;
         }
     }
-    const int R = PF_WAVES / S;
-    const int gx = (d.O + 16 * R - 1) / (16 * R), gy = (T + 16 * btt - 1) / (16 * btt);
+    if (!best)
+        return SBVR_E_UNSUPPORTED;
     PrefillArgs a = {(const uint32_t *)planes_dev, (const uint16_t *)coeffs_dev, X, Y, d.O, d.I, T, d.n_tiles,
-                     d.n_gblocks, d.G, (d.G + S - 1) / S, S};
-    const size_t front = (size_t)S * 2 * pf_xtile(btt);
-    const size_t red = (size_t)R * (S / 2) * btt * 4 * 64 * 4;
-    const size_t lds = (front > red ? front : red) + (size_t)PF_WAVES * 16 * ((1u << d.k) + PF_LUT_PAD) * 2;
+                     d.n_gblocks, d.G, (d.G + slices - 1) / slices};
+    size_t lds, red;  // activation stages; the partial sums reuse them
+    int waves = PF_WAVES;
+    if (best->rt) {
+        lds = (size_t)slices * 2 * (32 * best->tt * GROUP * 2 / best->st);
+        red = (size_t)best->r * (slices / 2) * best->rt * best->tt * 16 * 64 * 4;
+    } else {
+        waves = slices;
+        lds = (size_t)slices * 2 * ((min(T, 16 * best->tt) + 3) / 4) * 1024;
+        red = (size_t)slices * best->tt * 4 * 64 * 4;
+    }
+    lds = lds > red ? lds : red;
     if (lds > PF_LDS_MAX)
         return SBVR_E_UNSUPPORTED;
-    const void *fn = d.k == 4   ? prefill_kernel_for<4>(btt)
-                     : d.k == 3 ? prefill_kernel_for<3>(btt)
-                     : d.k == 2 ? prefill_kernel_for<2>(btt)
-                                : prefill_kernel_for<1>(btt);
+    const void *fn = d.k == 4   ? prefill_kernel_for<4>(*best)
+                     : d.k == 3 ? prefill_kernel_for<3>(*best)
+                     : d.k == 2 ? prefill_kernel_for<2>(*best)
+                                : prefill_kernel_for<1>(*best);
     void *args[] = {&a};
-    return launch_kernel(fn, dim3(gx, gy), dim3(64 * PF_WAVES), lds, stream, args);
+    return launch_kernel(fn, dim3(gx, gy), dim3(64 * waves), lds, stream, args);
 }
 
 }  // namespace sbvr

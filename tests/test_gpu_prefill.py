@@ -284,3 +284,47 @@ def test_prefill_random_shapes(sb, O, G, k, T, seed):
     assert worst <= TOL, worst
     if I >= 512:
         check(Y, X, planes, coeffs, rows=rows, what=f"random {O}x{I} k={k} T={T}")
+
+
+# One case per launch shape of the two prefill kernels -- workgroups of 16 rows
+# (8 or 16 wavefronts, 16- or 32-token tiles), then (column tiles, token tiles,
+# row groups) = (1,1,1), (1,2,1), (1,2,2), (1,2,4), (1,4,2), (1,4,4), (1,4,8)
+# and (2,4,8) -- with ragged rows, tokens and last gblocks, single groups and
+# more wavefronts than groups.
+SHAPE_CASES = [(1, 256, 2), (37, 640, 5), (1, 128, 2), (257, 2304, 13), (97, 128, 577), (116, 1152, 513),
+               (210, 768, 581), (213, 1152, 548), (442, 768, 588), (584, 1152, 419), (1045, 384, 369),
+               (4120, 1152, 66), (897, 128, 570), (8381, 1152, 67), (5381, 384, 364), (8559, 2432, 70),
+               (11057, 512, 129), (11018, 1152, 137), (11293, 128, 130), (13300, 1152, 263), (13060, 128, 518),
+               (14666, 1152, 516)]
+
+
+@pytest.mark.parametrize("k", [1, 2, 3, 4])
+@pytest.mark.parametrize("O,I,T", SHAPE_CASES)
+def test_prefill_launch_shapes(sb, O, I, T, k):
+    """Sampled rows, every token, against the binary64 product of the rounded
+    weights.  Every third row has coefficients 12 binades apart (sums that are
+    not exact in binary32), and the first tokens are unit vectors, whose
+    outputs are the weights themselves.  Bound per output: half a unit in the
+    last place of the result, and at most I + 16 binary32 additions (the
+    K-slices' included), each off by 2^-24 of the sum of the terms'
+    magnitudes."""
+    planes, coeffs = synth.random_sbvr(O, I, k, seed=O + 3 * I + 5 * k + T)
+    if k > 1:
+        c = coeffs[::3].view(np.float16)
+        c[:, :, 0] *= np.float16(2.0 ** -12)
+    W = packed(sb, planes, coeffs)
+    X = synth.activations(I, seed=O + T + k, batch=T)
+    unit = min(T - 1, 9)
+    cols = np.random.default_rng(I + k).integers(0, I, unit)
+    X[:unit] = 0
+    X[np.arange(unit), cols] = 1
+    rows = np.unique(np.r_[0, 1, 2, O // 2, O - 1, np.random.default_rng(O).integers(0, O, 59)] % O)
+    Y = run(sb, W, X)[:, rows]
+    w16 = fp16_weights(planes, coeffs, rows)
+    assert np.array_equal(Y[:unit], w16[:, cols].T), "weights"
+    X64 = X.astype(np.float64)
+    y = X64 @ w16.T
+    bound = 2.0 ** -11 * np.abs(y) + 2.0 ** -24 * (1 + (I + 16) * (np.abs(X64) @ np.abs(w16).T))
+    worst = (np.abs(Y - y) / bound).max()
+    log(f"prefill {O}x{I} k={k} T={T}: {worst:.3f} of the bound")
+    assert worst <= 1
