@@ -7,20 +7,28 @@
 // through a D-deep register ring loaded with buffer descriptors bounded by
 // the workgroup's tile range (loads past the end read zero, no traffic).
 //
-// Matrix-core formulation.  One 16x16x128 fp4 x fp8 instruction per (tile,
-// group, column set): the 128 k-slots are one whole group (its four plane
-// words, one per 32-slot k-block), rows are (tile row, plane) and the 16
-// columns are (vector, limb) with four columns per vector -- the four E5M2
-// limbs of its activations -- so a column set serves four vectors (B <= 4:
-// one set, B <= 8: two).  The device layout gives lane (row m, k-block b) the four
+// Matrix-core formulation.  A 16x16x128 fp4 x fp8 instruction takes one whole
+// group in its 128 k-slots (its four plane words, one per 32-slot k-block) and
+// (tile row, plane) in its rows; the activations of each vector are four E5M2
+// limbs.  For B <= 4 the 16 columns are (vector, limb) and a group takes one
+// instruction.  For B <= 8 a vector has two columns, each the sum of two
+// limbs: the group takes two chained instructions (the smaller limb first)
+// into one result.  The device layout gives lane (row m, k-block b) the four
 // words of group b; a 4 x 4 cross-lane transpose turns that into word b of
-// the four groups, i.e. the A operands of the four instructions of an item.
+// the four groups, i.e. the A operands of an item's four groups.
+//
+// Why two limbs share a column at B > 4: with a column per limb, eight vectors
+// took two results per group and 32 coefficient multiply-adds per lane and
+// item; chained they take one and 16 for the same eight instructions
+// (interleaved, 70B layer at B = 8 212 -> 186 us, 8B down 21.7 -> 20.2 us per
+// call, an 8B layer 73.5 -> 71.6).  What bounds the kernel at B = 8 is the
+// activation build (about 560 vector instructions per gblock, wavefront and
+// workgroup), then the vector work per item.
 //
 // Each lane applies the coefficients of its four D rows (the planes of 1, 2 or
 // 4 tile rows) for every group as one chain of fused multiply-adds and adds
-// the item's (row, vector, limb) partial to LDS; at the end the workgroup sums,
-// per output, the wavefronts in order and the four limb columns of its
-// vector (deterministic, no global workspace).
+// the item's (row, column) partial to LDS; at the end the workgroup sums, per
+// output, the wavefronts in order and the columns of its vector (deterministic, no global workspace).
 #include "device_ops.h"
 #include "launch.h"
 
@@ -54,18 +62,22 @@ namespace sbvr {
 #define SBVR_SBS_GROUPS 256
 #endif
 
-// vectors per column set, and the LDS staging per wavefront: the limbs of
-// two vectors at a time, [group][vector of the pair][limb][128 bytes], then
-// 256 zero bytes, read by the columns of absent vectors at a different 16
-// bytes per lane of a 16-lane group (a set of four vectors is staged in two
-// phases, which keeps eight wavefronts' staging within 35 KB)
-constexpr int SBS_VPS = 4;
+// Columns per vector of the 16-column result, and limbs chained into each.
+__host__ __device__ constexpr int sbs_cols(int nb) { return nb == 8 ? 2 : 4; }
+// LDS staging per wavefront: the limbs of VQ vectors at a time,
+// [group][vector][limb][128 bytes], then 256 zero bytes, read by the columns
+// of absent vectors at a different 16 bytes per lane of a 16-lane group.  Half
+// of the vectors is staged at a time (eight wavefronts' staging within 78 KB).
+// A limb's 128 bytes are padded to 144 and the groups lie an odd multiple of
+// 128 bytes apart: without that the lanes of a 16-byte read used half of the
+// 256-byte bank row, and an 8-byte write put all four groups into one half.
+__host__ __device__ constexpr int sbs_vq(int nb) { return nb == 8 ? 4 : 2; }
+constexpr int SBS_LIMB = GROUP + 16;
+__host__ __device__ constexpr int sbs_group_bytes(int nb) { return sbs_vq(nb) * 4 * SBS_LIMB | 128; }
+__host__ __device__ constexpr int sbs_stage_bytes(int nb) { return GB * sbs_group_bytes(nb) + 256; }
 // LDS a small-batch workgroup may use (of the 160 KiB of a gfx950 CU; one
 // workgroup per CU runs anyway at this kernel's register use)
 constexpr size_t SBS_LDS_MAX = 160 * 1024;
-__host__ __device__ constexpr int sbs_sets(int nb) { return (nb + SBS_VPS - 1) / SBS_VPS; }
-__host__ __device__ constexpr int sbs_vps(int nb) { return nb < SBS_VPS ? nb : SBS_VPS; }
-__host__ __device__ constexpr int sbs_stage_bytes(int) { return GB * 2 * 4 * GROUP + 256; }
 
 // max |x| over the wavefront for two activation vectors at once (eight
 // binary16 values per lane each): the magnitudes' bit patterns are compared as
@@ -177,8 +189,9 @@ __device__ __forceinline__ void fma_coefs(uint2 c, const v4f &d, float *acc)
 template <int K, int NB, int D, bool MULTI>
 __global__ void __launch_bounds__(512) gemm_sbs_kernel(GemvArgs a)
 {
-    constexpr int NS = sbs_sets(NB);
-    constexpr int VPS = sbs_vps(NB);
+    constexpr int CPV = sbs_cols(NB), CH = 4 / CPV;  // columns per vector, limbs per column
+    constexpr int VQ = sbs_vq(NB), NPH = NB / VQ;    // vectors staged at a time, phases
+    constexpr int LIMB = SBS_LIMB, GSTRIDE = sbs_group_bytes(NB);
     constexpr int STAGE = sbs_stage_bytes(NB);
     constexpr int ZERO0 = STAGE - 256;
     extern __shared__ __align__(16) unsigned char smem[];
@@ -188,7 +201,7 @@ __global__ void __launch_bounds__(512) gemm_sbs_kernel(GemvArgs a)
     const int B = a.B;  // vectors actually present (<= NB)
     unsigned char *stage = smem + wv * STAGE;
     constexpr int TR = tile_rows(K), NP = partials_per_lane<K>();
-    float *red = (float *)(smem + nw * STAGE);  // [tpw][nw][NS][TR rows][16 columns]
+    float *red = (float *)(smem + nw * STAGE);  // [tpw][nw][TR rows][16 columns]
 
     const int tile0 = blockIdx.x * a.tpw;
     const int ntl = min(a.tpw, a.n_tiles - tile0);
@@ -280,28 +293,26 @@ __global__ void __launch_bounds__(512) gemm_sbs_kernel(GemvArgs a)
 
     *(uint32_t *)(stage + ZERO0 + 4 * lane) = 0u;  // the zero region
     const int ZERO = ZERO0 + 16 * (lane & 15);
-    // B operand reads: lane (column n = lane%16 = (vector n/4, limb n%4),
-    // k-block lane/16) takes k = 16 kb + [0,16) and 64 + 16 kb + [0,16) of
-    // its vector's limb; absent vectors read the zero chunk.
+    // B operand reads: column n = lane%16 = (vector n/CPV, limbs CH * (n%CPV)
+    // ..), k-block lane/16, takes k = 16 kb + [0,16) and 64 + 16 kb + [0,16) of
+    // its vector's limbs; absent vectors read the zero chunk.
     const int n = lane & 15, kb = lane >> 4;
-    const int vb = n >> 2, limb = n & 3;
+    const int vb = n / CPV, limb = CH * (n % CPV);
     // limb writes: lane owns elements 8*lane.. of the gblock = group lane/16,
     // elements 8*(lane%16).. of it
-    const int wr_off = (lane >> 4) * (2 * 4 * GROUP) + 8 * (lane & 15);
+    const int wr_off = (lane >> 4) * GSTRIDE + 8 * (lane & 15);
     const int inv_alpha = inv_alpha_exp(lane & 3);
-    // staging phases per column set (vector pairs) and the lane's phase
-    constexpr int NPH = (VPS + 1) / 2;
-    const int my_phase = min(vb >> 1, NPH - 1);
+    const int my_phase = min(vb / VQ, NPH - 1);
 
-    v8i Bop[NS][GB];
-    float oscale[NS];  // 2^-sigma of the lane's vector, per set
+    v8i Bop[GB][CH];
+    float oscale;  // 2^-sigma of the lane's vector
     // With four or more vectors the activation maxima are reduced first, two
     // per register, so that the reductions' latencies overlap, and every
     // vector is split (vectors >= B hold zeros and give zero limbs in their
     // own slots, which no operand reads); with two, each vector present is
     // reduced and split in turn (measured faster there in the kernels that
-    // rebuild in the middle of the stream).  The limbs of a vector pair are
-    // staged, then the lanes of that pair's columns read their operands.
+    // rebuild in the middle of the stream).  The limbs of VQ vectors are
+    // staged, then the lanes of those vectors' columns read their operands.
     auto build = [&](const uint4 *X) {
         uint32_t amax2[(NB + 1) / 2] = {};
         if constexpr (NB >= 4) {
@@ -309,48 +320,41 @@ __global__ void __launch_bounds__(512) gemm_sbs_kernel(GemvArgs a)
             for (int p = 0; p < (NB + 1) / 2; ++p)
                 amax2[p] = wave_absmax2_bits(X[2 * p], X[2 * p + 1]);
         }
+        float os = 1.0f;
 #pragma unroll
-        for (int st = 0; st < NS; ++st) {
-            float inv_scale[VPS];
+        for (int ph = 0; ph < NPH; ++ph) {
 #pragma unroll
-            for (int ph = 0; ph < NPH; ++ph) {
+            for (int vv = 0; vv < VQ; ++vv) {
+                const int b = ph * VQ + vv;
+                if (NB >= 4 || b < B) {
+                    const float amax = NB >= 4 ? half_bits_to_float((amax2[b / 2] >> (16 * (b & 1))) & 0xffffu)
+                                               : wave_absmax_h(X[b]);
+                    const int sigma = scale_exponent(amax);
+                    const float inv_scale = ldexpf(1.0f, -sigma);
+                    os = vb == b ? inv_scale : os;
+                    const Limbs L = split_limbs(X[b], sigma, inv_alpha);
+                    unsigned char *dst = stage + wr_off + vv * 4 * LIMB;
 #pragma unroll
-                for (int vv = 0; vv < 2; ++vv) {
-                    const int v = 2 * ph + vv;
-                    if (v >= VPS)
-                        break;
-                    const int b = st * SBS_VPS + v;
-                    inv_scale[v] = 1.0f;
-                    if (NB >= 4 || b < B) {
-                        const float amax = NB >= 4 ? half_bits_to_float((amax2[b / 2] >> (16 * (b & 1))) & 0xffffu)
-                                                   : wave_absmax_h(X[b]);
-                        const int sigma = scale_exponent(amax);
-                        inv_scale[v] = ldexpf(1.0f, -sigma);
-                        const Limbs L = split_limbs(X[b], sigma, inv_alpha);
-                        unsigned char *dst = stage + wr_off + vv * 4 * GROUP;
-#pragma unroll
-                        for (int j = 0; j < 4; ++j)
-                            *(uint2 *)(dst + j * GROUP) = make_uint2(L.l[j][0], L.l[j][1]);
-                    }
-                }
-                // same wavefront: the reads below follow these writes, and the
-                // next phase's writes follow the reads
-                if (my_phase == ph) {
-                    const bool act = vb < VPS && st * SBS_VPS + vb < B;
-#pragma unroll
-                    for (int g = 0; g < GB; ++g) {
-                        const int lo = act ? ((g * 2 + (vb & 1)) * 4 + limb) * GROUP + 16 * kb : ZERO;
-                        const int hi = act ? lo + 64 : ZERO;
-                        Bop[st][g] = lds_operand(stage + lo, stage + hi);
-                    }
+                    for (int j = 0; j < 4; ++j)
+                        *(uint2 *)(dst + j * LIMB) = make_uint2(L.l[j][0], L.l[j][1]);
                 }
             }
-            float os = inv_scale[0];
+            // same wavefront: the reads below follow these writes, and the
+            // next phase's writes follow the reads
+            if (my_phase == ph) {
+                const bool act = vb < B;
 #pragma unroll
-            for (int v = 1; v < VPS; ++v)
-                os = vb == v ? inv_scale[v] : os;
-            oscale[st] = os;
+                for (int g = 0; g < GB; ++g)
+#pragma unroll
+                    for (int c = 0; c < CH; ++c) {
+                        const int at = g * GSTRIDE + ((vb % VQ) * 4 + limb + c) * LIMB + 16 * kb;
+                        const int lo = act ? at : ZERO;
+                        const int hi = act ? at + 64 : ZERO;
+                        Bop[g][c] = lds_operand(stage + lo, stage + hi);
+                    }
+            }
         }
+        oscale = os;
     };
     build(Xc);
     uint4 Xn[MULTI ? NB : 1];
@@ -358,10 +362,10 @@ __global__ void __launch_bounds__(512) gemm_sbs_kernel(GemvArgs a)
         load_x(Xn, wv + nw);
     __builtin_amdgcn_sched_barrier(0);
 
-    // red offset of this lane's (row, column) partials: column n = (vector,
-    // limb) of its set; the four limbs of a vector are added in the final sum
-    float *red_w = red + (wv * NS * TR + (lane >> 4) * NP) * 16 + n;
-    const int red_tile = nw * NS * TR * 16;
+    // red offset of this lane's (row, column) partials; the CPV columns of a
+    // vector are added in the final sum
+    float *red_w = red + (wv * TR + (lane >> 4) * NP) * 16 + n;
+    const int red_tile = nw * TR * 16;
     int cur_i = 0, cur_gb = wv;
     for (int m0 = 0; m0 < n_items; m0 += D) {
 #pragma unroll
@@ -379,36 +383,34 @@ __global__ void __launch_bounds__(512) gemm_sbs_kernel(GemvArgs a)
             }
             const uint4 pw = transpose_rows4(P[j]);
             const uint32_t words[GB] = {pw.x, pw.y, pw.z, pw.w};
-            v4f d[GB][NS];
+            v4f d[GB];
 #pragma unroll
             for (int g = 0; g < GB; ++g) {
                 const v8i A = fp4_operand(words[g]);
+                d[g] = v4f{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int st = 0; st < NS; ++st)
-                    d[g][st] = mfma_fp4_fp8<false>(A, Bop[st][g], v4f{0.f, 0.f, 0.f, 0.f});
+                for (int c = CH - 1; c >= 0; --c)  // smaller limb first
+                    d[g] = mfma_fp4_fp8<false>(A, Bop[g][c], d[g]);
             }
             const CoefGroups<K> cr = C[j];
             const unsigned co_next = issue_p(j);
+            // the lane's (tile row, column) partials of the item: every
+            // group's coefficients chained into one accumulator
+            float acc[NP];
 #pragma unroll
-            for (int st = 0; st < NS; ++st) {
-                // the lane's (tile row, vector, limb) partials of the item:
-                // every group's coefficients chained into one accumulator
-                float acc[NP];
+            for (int p = 0; p < NP; ++p)
+                acc[p] = 0.f;
 #pragma unroll
-                for (int p = 0; p < NP; ++p)
-                    acc[p] = 0.f;
+            for (int g = 0; g < GB; ++g)
+                fma_coefs<K>(coef_group<K>(cr, g), d[g], acc);
+            if (valid) {
+                float *r = red_w + cur_i * red_tile;
 #pragma unroll
-                for (int g = 0; g < GB; ++g)
-                    fma_coefs<K>(coef_group<K>(cr, g), d[g][st], acc);
-                if (valid) {
-                    float *r = red_w + cur_i * red_tile + st * TR * 16;
-#pragma unroll
-                    for (int p = 0; p < NP; ++p) {
-                        if (!MULTI || cur_gb == wv)
-                            r[p * 16] = acc[p] * oscale[st];
-                        else
-                            r[p * 16] += acc[p] * oscale[st];
-                    }
+                for (int p = 0; p < NP; ++p) {
+                    if (!MULTI || cur_gb == wv)
+                        r[p * 16] = acc[p] * oscale;
+                    else
+                        r[p * 16] += acc[p] * oscale;
                 }
             }
             issue_c(j, co_next);
@@ -428,12 +430,16 @@ __global__ void __launch_bounds__(512) gemm_sbs_kernel(GemvArgs a)
         const int b = idx / rows, lr = idx % rows;
         const int o = row_base + lr;
         if (o < a.O) {
-            const int st = b / SBS_VPS, v = b % SBS_VPS;
-            const float *r = red + (lr / TR) * red_tile + (st * TR + lr % TR) * 16 + 4 * v;
+            const float *r = red + (lr / TR) * red_tile + (lr % TR) * 16 + CPV * b;
             float s = 0.f;
             for (int w = 0; w < nw; ++w) {
-                const float4 q = *(const float4 *)(r + w * NS * TR * 16);  // the vector's four limbs
-                s += (q.x + q.y) + (q.z + q.w);
+                if constexpr (CPV == 2) {
+                    const float2 q = *(const float2 *)(r + w * TR * 16);
+                    s += q.x + q.y;
+                } else {
+                    const float4 q = *(const float4 *)(r + w * TR * 16);
+                    s += (q.x + q.y) + (q.z + q.w);
+                }
             }
             a.y[(size_t)b * a.O + o] = __half_as_ushort(__float2half_rn(s));
         }
@@ -476,7 +482,7 @@ int launch_gemm_sbs(const Dims &d, const void *planes_dev, const void *coeffs_de
     const int waves = gpw > 1 ? SBVR_SBS_MAX_WAVES : (d.n_gblocks + gpw - 1) / gpw;
     // tiles per workgroup, capped so that dynamic LDS stays within SBS_LDS_MAX
     const size_t fixed = (size_t)waves * sbs_stage_bytes(nb);
-    const size_t per_tile = (size_t)waves * sbs_sets(nb) * d.tr * 16 * 4;
+    const size_t per_tile = (size_t)waves * d.tr * 16 * 4;
     const int max_tpw = (int)((SBS_LDS_MAX - fixed) / per_tile);
     const int tpw = min((d.n_tiles + SBVR_SBS_GROUPS - 1) / SBVR_SBS_GROUPS, max_tpw);
     const int grid = (d.n_tiles + tpw - 1) / tpw;

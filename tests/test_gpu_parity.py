@@ -185,6 +185,22 @@ def test_small_batch_low_bit(sb, k):
     assert max(rel_err(Y[b], Y_ref[b]) for b in range(6)) <= TOL
 
 
+@pytest.mark.parametrize("k", [1, 2, 3, 4])
+@pytest.mark.parametrize("O,I", [(65, 128), (257, 4096), (130, 4736)])  # one group, full gblocks, ragged and several per wavefront
+def test_small_batch_every_width(sb, O, I, k):
+    """Every B: the kernels' vector counts, the columns of absent vectors and
+    (B > 4) the columns that hold two limbs, on activations whose limbs are
+    all occupied."""
+    planes, coeffs = synth.random_sbvr(O, I, k, seed=O + I + k)
+    X8 = synth.activations(I, seed=I + k + synth.X_SEED_OFFSET, batch=8)
+    W = packed(sb, planes, coeffs)
+    Y_ref = oracle.sbvr_gemv(planes, coeffs, X8)
+    for B in range(2, 9):
+        Y = run_gemm(sb, W, X8[:B].copy())
+        for b in range(B):
+            assert rel_err(Y[b], Y_ref[b]) <= TOL, (B, b)
+
+
 # --------------------------------------------------------------------------
 # Structured inputs with closed-form answers
 # --------------------------------------------------------------------------
