@@ -63,7 +63,7 @@ namespace sbvr {
 #endif
 
 // Columns per vector of the 16-column result, and limbs chained into each.
-__host__ __device__ constexpr int sbs_cols(int nb) { return nb == 8 ? 2 : 4; }
+__host__ __device__ constexpr int sbs_cols(int nb) { return nb > 4 ? 2 : 4; }
 // LDS staging per wavefront: the limbs of VQ vectors at a time,
 // [group][vector][limb][128 bytes], then 256 zero bytes, read by the columns
 // of absent vectors at a different 16 bytes per lane of a 16-lane group.  Half
@@ -71,7 +71,7 @@ __host__ __device__ constexpr int sbs_cols(int nb) { return nb == 8 ? 2 : 4; }
 // A limb's 128 bytes are padded to 144 and the groups lie an odd multiple of
 // 128 bytes apart: without that the lanes of a 16-byte read used half of the
 // 256-byte bank row, and an 8-byte write put all four groups into one half.
-__host__ __device__ constexpr int sbs_vq(int nb) { return nb == 8 ? 4 : 2; }
+__host__ __device__ constexpr int sbs_vq(int nb) { return nb > 4 ? 4 : 2; }
 constexpr int SBS_LIMB = GROUP + 16;
 __host__ __device__ constexpr int sbs_group_bytes(int nb) { return sbs_vq(nb) * 4 * SBS_LIMB | 128; }
 __host__ __device__ constexpr int sbs_stage_bytes(int nb) { return GB * sbs_group_bytes(nb) + 256; }
@@ -190,7 +190,7 @@ template <int K, int NB, int D, bool MULTI>
 __global__ void __launch_bounds__(512) gemm_sbs_kernel(GemvArgs a)
 {
     constexpr int CPV = sbs_cols(NB), CH = 4 / CPV;  // columns per vector, limbs per column
-    constexpr int VQ = sbs_vq(NB), NPH = NB / VQ;    // vectors staged at a time, phases
+    constexpr int VQ = sbs_vq(NB), NPH = (NB + VQ - 1) / VQ;  // vectors staged at a time, phases
     constexpr int LIMB = SBS_LIMB, GSTRIDE = sbs_group_bytes(NB);
     constexpr int STAGE = sbs_stage_bytes(NB);
     constexpr int ZERO0 = STAGE - 256;
@@ -306,7 +306,7 @@ __global__ void __launch_bounds__(512) gemm_sbs_kernel(GemvArgs a)
 
     v8i Bop[GB][CH];
     float oscale;  // 2^-sigma of the lane's vector
-    // With four or more vectors the activation maxima are reduced first, two
+    // With three or more vectors the activation maxima are reduced first, two
     // per register, so that the reductions' latencies overlap, and every
     // vector is split (vectors >= B hold zeros and give zero limbs in their
     // own slots, which no operand reads); with two, each vector present is
@@ -315,10 +315,10 @@ __global__ void __launch_bounds__(512) gemm_sbs_kernel(GemvArgs a)
     // staged, then the lanes of those vectors' columns read their operands.
     auto build = [&](const uint4 *X) {
         uint32_t amax2[(NB + 1) / 2] = {};
-        if constexpr (NB >= 4) {
+        if constexpr (NB >= 3) {
 #pragma unroll
             for (int p = 0; p < (NB + 1) / 2; ++p)
-                amax2[p] = wave_absmax2_bits(X[2 * p], X[2 * p + 1]);
+                amax2[p] = wave_absmax2_bits(X[2 * p], X[2 * p + 1 < NB ? 2 * p + 1 : 2 * p]);
         }
         float os = 1.0f;
 #pragma unroll
@@ -326,8 +326,10 @@ __global__ void __launch_bounds__(512) gemm_sbs_kernel(GemvArgs a)
 #pragma unroll
             for (int vv = 0; vv < VQ; ++vv) {
                 const int b = ph * VQ + vv;
-                if (NB >= 4 || b < B) {
-                    const float amax = NB >= 4 ? half_bits_to_float((amax2[b / 2] >> (16 * (b & 1))) & 0xffffu)
+                if (b >= NB)
+                    break;
+                if (NB >= 3 || b < B) {
+                    const float amax = NB >= 3 ? half_bits_to_float((amax2[b / 2] >> (16 * (b & 1))) & 0xffffu)
                                                : wave_absmax_h(X[b]);
                     const int sigma = scale_exponent(amax);
                     const float inv_scale = ldexpf(1.0f, -sigma);
@@ -446,8 +448,12 @@ __global__ void __launch_bounds__(512) gemm_sbs_kernel(GemvArgs a)
     }
 }
 
-// Kernels are compiled for NB = 2, 4 and 8 vectors; a call with B vectors
-// runs the smallest NB >= B (absent vectors are neither read nor written).
+// Kernels are compiled for NB = 2, 3, 4, 6 and 8 vectors; a call with B vectors
+// runs the smallest NB >= B (absent vectors are not written).  The activation
+// build is paid for NB vectors, and a branch that skips the absent ones cost
+// about 2 % where none is absent (eight 8B layers at B = 8 585 against 571 us).
+// Against 2, 4 and 8 alone (interleaved): eight 8B layers at k = 3, B = 3 414
+// -> 394 us; four at k = 4, B = 5, with the chained limbs, 292 -> 260.
 template <int K, int NB, int D>
 static const void *sbs_kernel_for(bool multi)
 {
@@ -458,7 +464,9 @@ template <int K, int D>
 static const void *sbs_kernel_kd(int nb, bool multi)
 {
     return nb == 2   ? sbs_kernel_for<K, 2, D>(multi)
+           : nb == 3 ? sbs_kernel_for<K, 3, D>(multi)
            : nb == 4 ? sbs_kernel_for<K, 4, D>(multi)
+           : nb == 6 ? sbs_kernel_for<K, 6, D>(multi)
                      : sbs_kernel_for<K, 8, D>(multi);
 }
 
@@ -466,8 +474,9 @@ template <int K>
 static const void *sbs_kernel_k(int nb, bool multi, bool long_ring)
 {
     if (multi && nb <= 4)
-        return nb == 2 ? (const void *)gemm_sbs_kernel<K, 2, SBVR_SBS_DEPTH_MULTI_SMALL, true>
-                       : (const void *)gemm_sbs_kernel<K, 4, SBVR_SBS_DEPTH_MULTI_SMALL, true>;
+        return nb == 2   ? (const void *)gemm_sbs_kernel<K, 2, SBVR_SBS_DEPTH_MULTI_SMALL, true>
+               : nb == 3 ? (const void *)gemm_sbs_kernel<K, 3, SBVR_SBS_DEPTH_MULTI_SMALL, true>
+                         : (const void *)gemm_sbs_kernel<K, 4, SBVR_SBS_DEPTH_MULTI_SMALL, true>;
     return long_ring ? sbs_kernel_kd<K, SBVR_SBS_DEPTH_LONG>(nb, multi)
                      : sbs_kernel_kd<K, SBVR_SBS_DEPTH_SHORT>(nb, multi);
 }
@@ -475,7 +484,7 @@ static const void *sbs_kernel_k(int nb, bool multi, bool long_ring)
 int launch_gemm_sbs(const Dims &d, const void *planes_dev, const void *coeffs_dev,
                     const uint16_t *X, uint16_t *Y, int B, hipStream_t stream)
 {
-    const int nb = B <= 2 ? 2 : (B <= 4 ? 4 : 8);
+    const int nb = B <= 4 ? (B < 2 ? 2 : B) : (B <= 6 ? 6 : 8);
     const int gpw = (d.n_gblocks + SBVR_SBS_MAX_WAVES - 1) / SBVR_SBS_MAX_WAVES;
     // several gblocks per wavefront: all eight wavefronts, so that the strided
     // gblock assignment balances the four SIMDs
