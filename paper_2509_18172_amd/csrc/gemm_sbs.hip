@@ -25,10 +25,22 @@
 // activation build (about 560 vector instructions per gblock, wavefront and
 // workgroup), then the vector work per item.
 //
+// The binary32 sum of one limb over a group is exact for elements down to about
+// 2^-15 of the block's maximum, that of two limbs down to about 2^-12 (six bits
+// per element instead of three); below that it is rounded.  At B > 4 and k > 1
+// an item's coefficient chain is therefore split in two, whose fewer roundings
+// outweigh that one.  Against 64 bits, on sums that cancel to 2^-20 of their
+// terms (normal activations, one in a thousand ten times as large), the error
+// is 0.87-1.01 of a column per limb's (one chain: 1.00-1.09), for 0.1 % of the
+// time.  At k = 1, where a chain has only four terms, two gain nothing
+// (0.97-1.04 either way).  Without cancellation the binary16 output's rounding
+// is all there is to see (2.1e-4 in every variant).
+//
 // Each lane applies the coefficients of its four D rows (the planes of 1, 2 or
 // 4 tile rows) for every group as one chain of fused multiply-adds and adds
 // the item's (row, column) partial to LDS; at the end the workgroup sums, per
-// output, the wavefronts in order and the columns of its vector (deterministic, no global workspace).
+// output, the wavefronts in order and the columns of its vector
+// (deterministic, no global workspace).
 #include "device_ops.h"
 #include "launch.h"
 
@@ -396,15 +408,22 @@ __global__ void __launch_bounds__(512) gemm_sbs_kernel(GemvArgs a)
             }
             const CoefGroups<K> cr = C[j];
             const unsigned co_next = issue_p(j);
-            // the lane's (tile row, column) partials of the item: every
-            // group's coefficients chained into one accumulator
-            float acc[NP];
+            // the lane's (tile row, column) partials of the item: the groups'
+            // coefficients chained into one accumulator, or two (see the top
+            // of the file) added at the end
+            constexpr bool TWO = CH > 1 && K > 1;
+            float acc[NP], acc2[NP];
 #pragma unroll
             for (int p = 0; p < NP; ++p)
-                acc[p] = 0.f;
+                acc[p] = acc2[p] = 0.f;
 #pragma unroll
             for (int g = 0; g < GB; ++g)
-                fma_coefs<K>(coef_group<K>(cr, g), d[g], acc);
+                fma_coefs<K>(coef_group<K>(cr, g), d[g], TWO && g >= GB / 2 ? acc2 : acc);
+            if constexpr (TWO) {
+#pragma unroll
+                for (int p = 0; p < NP; ++p)
+                    acc[p] += acc2[p];
+            }
             if (valid) {
                 float *r = red_w + cur_i * red_tile;
 #pragma unroll

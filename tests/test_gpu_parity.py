@@ -201,6 +201,79 @@ def test_small_batch_every_width(sb, O, I, k):
             assert rel_err(Y[b], Y_ref[b]) <= TOL, (B, b)
 
 
+def cancelling_inputs(O, I, k, B, kind, seed):
+    """Weights whose second half of groups repeats the first in another order,
+    and activations that take the first half's negatives there, one in a hundred
+    off by a unit in the last place: results of about 2^-20 of their terms, so
+    that the output's rounding (the results are not subnormal) hides little of
+    the sums'.  kind: normal
+    activations, one in a thousand ten times as large, or magnitudes spread over
+    e^(3 z) (elements below 2^-12 of their block's maximum)."""
+    rng = np.random.default_rng(seed)
+    G, H = I // 128, I // 256
+    planes, coeffs = synth.random_sbvr(O, I, k, seed=seed, coeff_sigma=0.5)
+    perm = rng.permutation(H)
+    planes[:, H:2 * H] = planes[:, perm]
+    coeffs[:, H:2 * H] = coeffs[:, perm]
+    x = rng.standard_normal((B, G, 128))
+    if kind == "wide":
+        x = np.sign(x) * np.exp(3 * rng.standard_normal(x.shape) - 4)
+    else:
+        x = np.where(rng.random(x.shape) < 0.001, 10 * x, x)
+    x = x.astype(np.float16)
+    flip = (rng.random((B, H, 128)) < 0.01) & (np.abs(x[:, perm]) > 1e-3)
+    x[:, H:2 * H] = ((-x[:, perm]).view(np.uint16) ^ flip).view(np.float16)
+    x[:, 2 * H:] = 0
+    return planes, coeffs, x.reshape(B, I)
+
+
+@pytest.mark.parametrize("k", [1, 2, 3, 4])
+@pytest.mark.parametrize("kind", ["normal", "wide"])
+@pytest.mark.parametrize("O,I", [(257, 4096), (130, 4864)])
+def test_small_batch_limb_sums_under_cancellation(sb, O, I, kind, k):
+    """B = 5..8 add two limbs in one column, B <= 4 keep one per column.  Every
+    output within the bound of its binary32 sums: half a unit in the last place;
+    2^-24 of the terms' magnitudes (a plane's coefficient times an activation)
+    for each addition a term passes through -- two groups of 128 limbs, 16
+    coefficients of an item, a wavefront's items, eight wavefronts and four
+    columns; and what the limbs leave out (less than 2^-27 of its block's largest
+    activation per element)."""
+    planes, coeffs, X = cancelling_inputs(O, I, k, 8, kind, O + I + k)
+    W = packed(sb, planes, coeffs)
+    y = oracle.sbvr_gemv(planes, coeffs, X)
+    mag = oracle.sbvr_gemv(planes, coeffs & 0x7fff, np.abs(X))
+    pad = np.zeros((8, -(-I // 512) * 512))
+    pad[:, :I] = np.abs(X)
+    left = np.repeat(pad.reshape(8, -1, 512).max(-1), 512, axis=1)[:, :I] * 2.0 ** -27
+    lost = oracle.sbvr_gemv(planes, coeffs & 0x7fff, np.ones((1, I), np.float16))[0][None] * left.max(1)[:, None]
+    adds = 2 * 128 + 16 + -(-I // 4096) + 8 + 4
+    bound = 2.0 ** -11 * np.abs(y) + 2.0 ** -24 * (1 + adds * mag) + lost
+    for B in range(2, 9):
+        Y = run_gemm(sb, W, X[:B].copy())
+        worst = (np.abs(Y - y[:B]) / bound[:B]).max()
+        log(f"small batch cancelling {O}x{I} k={k} {kind} B={B}: {worst:.4f} of the bound")
+        assert worst <= 1, (B, worst)
+
+
+@pytest.mark.parametrize("k", [3, 4])
+@pytest.mark.parametrize("I", [4096, 14336])
+def test_small_batch_limb_pairs_lose_nothing(sb, k, I):
+    """Two limbs per column (B = 8) are no further from 64 bits than one (the
+    same vectors in two calls of B = 4): root mean square of the error over the
+    terms' magnitudes, on sums that cancel."""
+    planes, coeffs, X = cancelling_inputs(1024, I, k, 8, "normal", 11 * k + I)
+    W = packed(sb, planes, coeffs)
+    y = oracle.sbvr_gemv(planes, coeffs, X)
+    mag = oracle.sbvr_gemv(planes, coeffs & 0x7fff, np.abs(X))
+
+    def rms(Y):
+        return np.sqrt((((Y - y) / mag) ** 2).mean())
+    two = rms(run_gemm(sb, W, X))
+    one = rms(np.concatenate([run_gemm(sb, W, X[:4].copy()), run_gemm(sb, W, X[4:].copy())]))
+    log(f"small batch 1024x{I} k={k}: error / terms {two:.3e} with two limbs per column, {one:.3e} with one")
+    assert two <= one
+
+
 # --------------------------------------------------------------------------
 # Structured inputs with closed-form answers
 # --------------------------------------------------------------------------
