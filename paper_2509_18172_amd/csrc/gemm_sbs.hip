@@ -503,7 +503,7 @@ static const void *sbs_kernel_k(int nb, bool multi, bool long_ring)
 int launch_gemm_sbs(const Dims &d, const void *planes_dev, const void *coeffs_dev,
                     const uint16_t *X, uint16_t *Y, int B, hipStream_t stream)
 {
-    const int nb = B <= 4 ? (B < 2 ? 2 : B) : (B <= 6 ? 6 : 8);
+    const int nb = B <= 4 ? B : (B <= 6 ? 6 : 8);
     const int gpw = (d.n_gblocks + SBVR_SBS_MAX_WAVES - 1) / SBVR_SBS_MAX_WAVES;
     // several gblocks per wavefront: all eight wavefronts, so that the strided
     // gblock assignment balances the four SIMDs
