@@ -40,6 +40,8 @@
 #include "launch.h"
 #include "row_decode.h"
 
+#include <math.h>
+
 namespace sbvr {
 
 constexpr size_t PF_LDS_MAX = 160 * 1024;  // LDS of one workgroup on gfx950
@@ -481,50 +483,77 @@ __global__ void __launch_bounds__(64 * NW) prefill_short_kernel(PrefillArgs a)
 }
 
 // Launch shapes.  prefill_kernel: rt, tt, r, st; prefill_short_kernel: rt = 0,
-// tt, r = the most wavefronts.  cost: the time of a launch in microseconds,
-// fitted for each shape to 3463 matrices and prompts on MI355X (16 .. 28672
-// rows, 128 .. 28672 columns, 1 .. 2048 tokens, k = 1 .. 4; the prediction is
-// within 20 % of the time in 90 % of them).  With w workgroups per CU (f = w,
-// c = w rounded up: the last round counts whole) and g groups per K-slice,
-//   prefill_kernel        [0] + [1] g + ([2] c + [3] f) g + [4] c
-//   prefill_short_kernel  [0] + [1] g + ([2] c + [3] f) g n / 16 + [4] c
-//                             + ([5] c + [6] f) g n x / 64
+// tt, r = the most wavefronts.  cost: the time of a launch in microseconds.
+// With f workgroups per CU (c = f rounded up), of which a CU holds `held` at
+// once (LDS, wavefronts, registers; r = f / held rounded up: the rounds), and g
+// groups per K-slice,
+//   prefill_kernel        [0] + [1] g + ([2] c + [3] f + [5] r) g + [4] c + [6] r
+//   prefill_short_kernel  [0] + [1] g + ([2] c + [3] f + [5] f x / 4) g n / 16
+//                             + ([6] + [7] x) r g + [4] c + [8] r
 // for n wavefronts and x loads of four tokens per group.  The shape with the
-// lowest cost runs.  Over those cases its choice takes 1.3 % more than the best
-// shape of each on average (7.7 % at the 95th percentile), and the launch is
-// 1.51 (k = 1) to 1.81 (k = 3) times as fast as the LDS-table kernels were
-// (geometric means; the least 0.91, a single-group matrix at k = 1).
-// Sixteen-wavefront workgroups are left to grids of one per CU: in larger ones
-// the fit misses that two of them do not share a CU (12778 x 1536, 13 tokens,
-// k = 3: 12.8 us against 9.4 with eight wavefronts).
+// lowest cost runs.
+//
+// Fitted on MI355X to the times of all twelve shapes on 3949 matrices and
+// prompts (1 .. 28672 rows, 128 .. 28672 columns, 1 .. 2048 tokens, k = 1 .. 4,
+// the sizes spread over their logarithms; each shape forced in turn, 2 to 40
+// launches back to back over rotating weights): a non-negative least-squares
+// fit of the relative error, then single steps of the constants that lower the
+// time of the chosen shape over the best one's.  k is left out: constants of
+// each k's own gained 0.1 %.  The choice takes 0.9 % more than the best shape
+// on average (6.1 % at the 95th percentile, 23 % at most; constants fitted to
+// 70 % of the cases, 0.9 % on the others).  Against the LDS-table kernels it
+// takes 0.64 (k = 1) to 0.54 (k = 3) of the time (geometric means); 2 of the
+// 3949 are slower, by 4 and 5 % (163 x 5632, 2038 tokens, and 15846 x 1408, 16
+// tokens, both k = 1).
+// What the terms are for: a fit without the rounds took a shape that a CU holds
+// once for one that shares it (18332 x 896, k = 2, 23 tokens 16.2 us instead of
+// 8.5; 11.4 with the LDS tables), and without the shape of 32 tokens and eight
+// row groups matrices of one group took up to 1.29 times the LDS tables' time
+// (6599 x 128, k = 1, 265 tokens 6.6 us instead of 4.1).
 struct PrefillShape {
     int rt, tt, r, st;
-    float cost[7];
+    int held;  // prefill_kernel: workgroups a CU holds at once (the short kernel's: see prefill_cost)
+    float cost[9];
 };
 
 static const PrefillShape PREFILL_SHAPES[] = {
-    {0, 1, 8, 1, {2.647f, 0.312f, 0.462f, 0.339f, 0.176f, 0.417f, 0.185f}},
-    {0, 1, 16, 1, {2.892f, 0.076f, 0.813f, 0.000f, 0.141f, 0.328f, 0.646f}},
-    {0, 2, 8, 1, {2.663f, 0.233f, 0.624f, 0.098f, 0.391f, 0.403f, 0.490f}},
-    {1, 1, 1, 1, {1.293f, 0.169f, 0.858f, 0.355f, 2.306f}},
-    {1, 2, 1, 2, {1.130f, 0.242f, 1.157f, 0.506f, 3.414f}},
-    {1, 2, 2, 1, {0.887f, 0.080f, 1.166f, 0.331f, 3.684f}},
-    {1, 2, 4, 1, {2.339f, 0.270f, 0.872f, 0.271f, 1.727f}},
-    {1, 4, 2, 2, {0.555f, 0.029f, 1.812f, 0.452f, 5.762f}},
-    {1, 4, 4, 1, {0.000f, 0.000f, 1.529f, 0.423f, 5.862f}},
-    {1, 4, 8, 1, {0.000f, 0.000f, 1.447f, 0.439f, 4.441f}},
-    {2, 4, 8, 1, {0.000f, 0.000f, 2.631f, 1.052f, 6.122f}},
+    {0, 1, 8, 1, 0, {1.811f, 0.268f, 0.509f, 0.377f, 0.164f, 0.226f, 0.000f, 0.060f, 0.379f}},
+    {0, 1, 16, 1, 0, {1.639f, 0.038f, 0.819f, 0.015f, 0.452f, 0.332f, 0.001f, 0.097f, 0.613f}},
+    {0, 2, 8, 1, 0, {1.247f, 0.310f, 0.333f, 0.674f, 0.344f, 0.001f, 0.002f, 0.075f, 0.915f}},
+    {1, 1, 1, 1, 1, {0.426f, 0.282f, 0.704f, 0.324f, 2.808f}},
+    {1, 2, 1, 2, 1, {0.010f, 0.004f, 1.727f, 0.025f, 4.068f}},
+    {1, 2, 2, 1, 1, {0.495f, 0.000f, 1.119f, 0.426f, 3.393f}},
+    {1, 2, 4, 1, 2, {1.901f, 0.359f, 0.508f, 0.615f, 1.448f, 0.140f, 0.813f}},
+    {1, 4, 2, 2, 1, {0.031f, 0.019f, 1.361f, 1.114f, 8.276f}},
+    {1, 4, 4, 1, 1, {2.741f, 0.027f, 1.088f, 0.987f, 4.261f}},
+    {1, 4, 8, 1, 1, {1.877f, 0.013f, 1.297f, 0.565f, 4.058f}},
+    {1, 1, 8, 1, 2, {1.871f, 0.604f, 0.210f, 0.414f, 1.210f, 0.002f, 0.000f}},
+    {2, 4, 8, 1, 1, {0.210f, 0.008f, 0.904f, 2.695f, 10.764f}},
 };
+
+// LDS of a launch: two activation stages per K-slice, which the partial sums
+// then reuse.
+static size_t prefill_lds(const PrefillShape &s, int T, int slices)
+{
+    const size_t stages = s.rt ? (size_t)slices * 2 * (32 * s.tt * GROUP * 2 / s.st)
+                               : (size_t)slices * 2 * ((min(T, 16 * s.tt) + 3) / 4) * 1024;
+    const size_t sums = s.rt ? (size_t)s.r * (slices / 2) * s.rt * s.tt * 16 * 64 * 4
+                             : (size_t)slices * s.tt * 4 * 64 * 4;
+    return stages > sums ? stages : sums;
+}
 
 static double prefill_cost(const PrefillShape &s, const Dims &d, int T, int slices, double wg)
 {
-    const double f = wg / PF_CUS, c = (double)(long long)((wg + PF_CUS - 1) / PF_CUS);
-    const double g = (d.G + slices - 1) / slices;
+    const double f = wg / PF_CUS, g = (d.G + slices - 1) / slices;
+    // short kernel: at most 64 registers, so 32 wavefronts per CU
+    const int held = s.rt ? s.held : max(1, min((int)(PF_LDS_MAX / prefill_lds(s, T, slices)), 32 / slices));
+    const double c = ceil(f), r = ceil(f / held);
+    const float *k = s.cost;
     if (s.rt)
-        return s.cost[0] + s.cost[1] * g + (s.cost[2] * c + s.cost[3] * f) * g + s.cost[4] * c;
+        return k[0] + k[1] * g + (k[2] * c + k[3] * f + k[5] * r) * g + k[4] * c + k[6] * r;
     const double x = (min(T, 16 * s.tt) + 3) / 4;
-    return s.cost[0] + s.cost[1] * g + (s.cost[2] * c + s.cost[3] * f) * g * slices / 16 + s.cost[4] * c +
-           (s.cost[5] * c + s.cost[6] * f) * g * slices * x / 64;
+    return k[0] + k[1] * g + (k[2] * c + k[3] * f + k[5] * f * x / 4) * g * slices / 16 +
+           (k[6] + k[7] * x) * r * g + k[4] * c + k[8] * r;
 }
 
 template <int K>
@@ -537,7 +566,7 @@ static const void *prefill_kernel_for(const PrefillShape &s)
     if (s.rt == 2)
         return (const void *)prefill_kernel<K, 2, 4, 8, 1>;
     if (s.tt == 1)
-        return (const void *)prefill_kernel<K, 1, 1, 1, 1>;
+        return s.r == 1 ? (const void *)prefill_kernel<K, 1, 1, 1, 1> : (const void *)prefill_kernel<K, 1, 1, 8, 1>;
     if (s.tt == 2)
         return s.r == 1   ? (const void *)prefill_kernel<K, 1, 2, 1, 2>
                : s.r == 2 ? (const void *)prefill_kernel<K, 1, 2, 2, 1>
@@ -547,52 +576,62 @@ static const void *prefill_kernel_for(const PrefillShape &s)
                       : (const void *)prefill_kernel<K, 1, 4, 8, 1>;
 }
 
-int launch_prefill(const Dims &d, const void *planes_dev, const void *coeffs_dev, const uint16_t *X, uint16_t *Y,
-                   int T, hipStream_t stream)
+// The launch of a call: its shape (null: none can take it), K-slices and grid.
+struct PrefillLaunch {
+    const PrefillShape *shape;
+    int slices, gx, gy;
+};
+
+static PrefillLaunch prefill_launch(const Dims &d, int T)
 {
-    const PrefillShape *best = nullptr;
+    PrefillLaunch best = {};
     double best_cost = 0;
-    int slices = 0, gx = 0, gy = 0;
     for (const PrefillShape &s : PREFILL_SHAPES) {
         const int sl = s.rt ? PF_WAVES / s.r : min(s.r, d.G);
         const int rows = s.rt ? 32 * s.rt * s.r : 16, tokens = s.rt ? 32 * s.tt : 16 * s.tt;
         const int x = (d.O + rows - 1) / rows, y = (T + tokens - 1) / tokens;
         if (y > 65535)  // (a grid's second dimension has 16 bits)
             continue;
-        if (!s.rt && s.r > PF_WAVES && (long long)x * y > PF_CUS)
-            continue;
         const double cost = prefill_cost(s, d, T, sl, (double)x * y);
-        if (!best || cost < best_cost) {
-            best = &s;
+        if (!best.shape || cost < best_cost) {
+            best = {&s, sl, x, y};
             best_cost = cost;
-            slices = sl;
-            gx = x;
-            gy = y;
         }
     }
-    if (!best)
+    return best;
+}
+
+int launch_prefill(const Dims &d, const void *planes_dev, const void *coeffs_dev, const uint16_t *X, uint16_t *Y,
+                   int T, hipStream_t stream)
+{
+    const PrefillLaunch l = prefill_launch(d, T);
+    if (!l.shape)
         return SBVR_E_UNSUPPORTED;
     PrefillArgs a = {(const uint32_t *)planes_dev, (const uint16_t *)coeffs_dev, X, Y, d.O, d.I, T, d.n_tiles,
-                     d.n_gblocks, d.G, (d.G + slices - 1) / slices};
-    size_t lds, red;  // activation stages; the partial sums reuse them
-    int waves = PF_WAVES;
-    if (best->rt) {
-        lds = (size_t)slices * 2 * (32 * best->tt * GROUP * 2 / best->st);
-        red = (size_t)best->r * (slices / 2) * best->rt * best->tt * 16 * 64 * 4;
-    } else {
-        waves = slices;
-        lds = (size_t)slices * 2 * ((min(T, 16 * best->tt) + 3) / 4) * 1024;
-        red = (size_t)slices * best->tt * 4 * 64 * 4;
-    }
-    lds = lds > red ? lds : red;
+                     d.n_gblocks, d.G, (d.G + l.slices - 1) / l.slices};
+    const size_t lds = prefill_lds(*l.shape, T, l.slices);
     if (lds > PF_LDS_MAX)
         return SBVR_E_UNSUPPORTED;
-    const void *fn = d.k == 4   ? prefill_kernel_for<4>(*best)
-                     : d.k == 3 ? prefill_kernel_for<3>(*best)
-                     : d.k == 2 ? prefill_kernel_for<2>(*best)
-                                : prefill_kernel_for<1>(*best);
+    const int waves = l.shape->rt ? PF_WAVES : l.slices;
+    const void *fn = d.k == 4   ? prefill_kernel_for<4>(*l.shape)
+                     : d.k == 3 ? prefill_kernel_for<3>(*l.shape)
+                     : d.k == 2 ? prefill_kernel_for<2>(*l.shape)
+                                : prefill_kernel_for<1>(*l.shape);
     void *args[] = {&a};
-    return launch_kernel(fn, dim3(gx, gy), dim3(64 * waves), lds, stream, args);
+    return launch_kernel(fn, dim3(l.gx, l.gy), dim3(64 * waves), lds, stream, args);
 }
 
 }  // namespace sbvr
+
+// Which launch shape a call takes, its index in PREFILL_SHAPES (-1: none), and
+// how many shapes there are: for the tests, not part of the C ABI.
+extern "C" int sbvr_test_prefill_shape(int O, int I, int k, int T)
+{
+    const sbvr::PrefillShape *s = sbvr::prefill_launch(sbvr::make_dims(O, I, k), T).shape;
+    return s ? (int)(s - sbvr::PREFILL_SHAPES) : -1;
+}
+
+extern "C" int sbvr_test_prefill_shapes(void)
+{
+    return (int)(sizeof(sbvr::PREFILL_SHAPES) / sizeof(sbvr::PREFILL_SHAPES[0]));
+}

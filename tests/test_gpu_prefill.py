@@ -109,21 +109,16 @@ def test_prefill_ragged(sb, O, I, k, T):
 def test_prefill_full_size_sampled(sb, O, I, T):
     """Llama-3-8B projection shapes (and the 70B q/o shape) at the
     benchmark's prompt lengths, on sampled rows (first and last included) and
-    every token; 256 tokens runs the long-prompt kernel with 8 activation
-    chunks per thread (4096 rows: 64-token tiles over four K-slices; 14336
-    rows: 128-token tiles over two)."""
+    every token."""
     planes, coeffs = synth.random_sbvr(O, I, 4, seed=O + 7 * I)
     X = synth.activations(I, seed=T + O, batch=T)
     rows = np.unique(np.r_[0, O - 1, np.random.default_rng(T).integers(0, O, 62)])
     check(run(sb, packed(sb, planes, coeffs), X), X, planes, coeffs, rows=rows, what=f"full {O}x{I} T={T}")
 
 
-# The long-prompt kernel (32 x 32 instructions; it runs from 96 tokens where
-# its grid has >= 192 workgroups): one case per launch shape the rule picks
-# -- (column tiles, token tiles, K-slices) = (1,1,1), (1,1,2), (1,1,4),
-# (1,2,1), (1,2,2), (1,4,1), (1,2,4) and (1,4,2) (8 activation chunks per
-# thread), (2,1,4), (2,2,2), then (1,4,1) with 240 workgroups and (2,1,2) --
-# with ragged row and token counts and k = 1..4.
+# Prompts of 100 to 1000 tokens on one to four groups, with ragged row and
+# token counts and k = 1..4 (which launch shapes they take is not the point
+# here; SHAPE_CASES below has every one).
 LONG_CASES = [(1500, 128, 1, 1000), (6144, 256, 2, 100), (1500, 512, 3, 256), (8192, 128, 4, 333),
               (6144, 256, 1, 200), (6144, 128, 3, 1000), (6144, 512, 2, 100), (8192, 256, 4, 333),
               (3000, 512, 1, 256), (12288, 256, 2, 300), (12288, 128, 2, 640), (12288, 256, 3, 160)]
@@ -151,14 +146,13 @@ def test_prefill_long_prompt_shapes(sb, O, I, k, T):
 
 
 def test_prefill_long_prompt_weights_bit_exact(sb):
-    """The long-prompt kernel multiplies the correctly rounded binary16
-    weights: unit tokens for the first 128 columns (T = 128, one K-slice
-    shape) and for all 512 (T = 512, another), ordinary and wide coefficient
-    spans (the binary64 table path); and all 512 columns of a 12288-row
-    matrix (the 1 x 4 x 1 shape)."""
+    """Long prompts multiply the correctly rounded binary16 weights: unit tokens
+    for the first 128 columns (T = 128) and for all 512 (T = 512), ordinary and
+    wide coefficient spans (the binary64 table path); and all 512 columns of a
+    12288-row matrix."""
     O12, I12 = 12288, 512
     planes, coeffs = synth.random_sbvr(O12, I12, 4, seed=76)
-    check_unit_tokens(sb, packed(sb, planes, coeffs), planes, coeffs, np.arange(I12), what="long 1x4 T=512")
+    check_unit_tokens(sb, packed(sb, planes, coeffs), planes, coeffs, np.arange(I12), what="long 12288 rows T=512")
     O, I, k = 4096, 512, 4
     planes, coeffs = synth.random_sbvr(O, I, k, seed=77)
     W = packed(sb, planes, coeffs)
@@ -226,13 +220,13 @@ def test_prefill_error_paths(sb):
 
 
 def test_prefill_graph_replays_match_eager(sb):
-    """Both prefill kernels (a 64-token and a 512-token prompt) captured in a
-    HIP graph, replayed three times with eager work in between: every replay
-    gives the eager bits."""
+    """Both prefill kernels (5 tokens: the 16-row one; 64 and 512: two shapes of
+    the other) captured in a HIP graph, replayed three times with eager work in
+    between: every replay gives the eager bits."""
     O, I = 4096, 1024
     planes, coeffs = synth.random_sbvr(O, I, 4, seed=91)
     W = packed(sb, planes, coeffs)
-    Xs = [dev(synth.activations(I, seed=92 + T, batch=T)) for T in (64, 512)]
+    Xs = [dev(synth.activations(I, seed=92 + T, batch=T)) for T in (5, 64, 512)]
     eager = [sb.gemm_prefill(W, X).clone() for X in Xs]
     outs = [torch.empty((X.shape[0], O), dtype=torch.float16, device="cuda") for X in Xs]
     s = torch.cuda.Stream()
@@ -254,7 +248,7 @@ def test_prefill_graph_replays_match_eager(sb):
 
 # Property test over random shapes and prompt lengths (Hypothesis,
 # derandomised: every run draws the same examples, no example database):
-# both prefill kernels and whatever long-prompt launch shape the rule picks.
+# both prefill kernels and whatever launch shape the rule picks.
 hypothesis = pytest.importorskip("hypothesis")
 from hypothesis import HealthCheck, given, settings  # noqa: E402
 from hypothesis import strategies as st  # noqa: E402
@@ -286,16 +280,22 @@ def test_prefill_random_shapes(sb, O, G, k, T, seed):
         check(Y, X, planes, coeffs, rows=rows, what=f"random {O}x{I} k={k} T={T}")
 
 
-# One case per launch shape of the two prefill kernels -- workgroups of 16 rows
-# (8 or 16 wavefronts, 16- or 32-token tiles), then (column tiles, token tiles,
-# row groups) = (1,1,1), (1,2,1), (1,2,2), (1,2,4), (1,4,2), (1,4,4), (1,4,8)
-# and (2,4,8) -- with ragged rows, tokens and last gblocks, single groups and
-# more wavefronts than groups.
+# Ragged rows, tokens and last gblocks, single groups and more wavefronts than
+# groups over every launch shape of the two prefill kernels
+# (test_prefill_launch_rule.py checks that each is taken): workgroups of 16 rows
+# with 8 or 16 wavefronts and 16- or 32-token tiles, then (column tiles, token
+# tiles, row groups) = (1,1,1), (1,2,1), (1,2,2), (1,2,4), (1,4,2), (1,4,4),
+# (1,4,8), (1,1,8) and (2,4,8).
 SHAPE_CASES = [(1, 256, 2), (37, 640, 5), (1, 128, 2), (257, 2304, 13), (97, 128, 577), (116, 1152, 513),
                (210, 768, 581), (213, 1152, 548), (442, 768, 588), (584, 1152, 419), (1045, 384, 369),
                (4120, 1152, 66), (897, 128, 570), (8381, 1152, 67), (5381, 384, 364), (8559, 2432, 70),
                (11057, 512, 129), (11018, 1152, 137), (11293, 128, 130), (13300, 1152, 263), (13060, 128, 518),
-               (14666, 1152, 516)]
+               (14666, 1152, 516),
+               # sixteen wavefronts: a full tile, two and a remainder, a partial one
+               (257, 4096, 16), (257, 4096, 35), (100, 3456, 7),
+               # 32-token tiles of the 16-row kernel, and the shapes the above leave out
+               (476, 896, 150), (1385, 256, 248), (369, 896, 338), (2246, 2944, 471), (3049, 896, 673),
+               (5986, 128, 680), (9005, 1152, 650)]
 
 
 @pytest.mark.parametrize("k", [1, 2, 3, 4])
