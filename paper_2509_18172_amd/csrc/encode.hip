@@ -52,14 +52,18 @@
 // ENC_RUN consecutive entries (neighbouring entries share r and s, so the
 // divisions of Eq. 4 are made once per (r, s)); in the scoring every lane takes
 // its two elements of one entry.  Where more than ENC_LIST entries of a chunk
-// survive (degenerate groups), lanes take entries instead and the elements run
-// in order, so such a group costs what an unscreened search does.
-// Bound: vector instruction issue (about 4600 of the ~7000 per group are the
-// bounds).  Measured on a 4096 x 4096 matrix, 1024 entries, encoding and
-// packing: k = 4 17.90 -> 1.50 ms, with the encoder cache at k = 3 7.53 ->
-// 0.91 ms, against scoring every entry by the definition (with pruning).
-// Groups whose entries are all alike (magnitudes below binary16's) keep every
-// entry and take what they took: k = 4 3.17 -> 3.16 ms for 1024 x 2048.
+// survive (degenerate groups), or more than enc_serial(k) sets are left after
+// the first one is scored, lanes take entries instead and the elements run in
+// order, so such a group costs about what an unscreened search does.  Grids of
+// a few entries are not screened at all (ENC_PLAIN_SUMS).
+// Bound: vector instruction issue, about 7600 instructions per group at k = 4,
+// of which about 4600 are the (binary32) bounds; 3200 at k = 1.  Measured
+// against scoring every entry by the definition (with pruning), 1024 entries,
+// N(0, 0.02^2), one value in a thousand at 8 sigma: 4096 x 4096, encoding and
+// packing, k = 4 17.9 -> 1.48 ms, with the encoder cache at k = 3 7.6 -> 0.91
+// ms; encoding alone at k = 1 3.5 -> 0.75 ms.  Groups whose entries are all
+// alike (magnitudes below binary16's) keep every entry: 1024 x 2048, k = 4 3.05
+// -> 2.26 ms, k = 1 0.50 -> 0.49.
 #include "device_ops.h"
 #include "f16_round.h"
 #include "launch.h"
@@ -149,20 +153,17 @@ __device__ __forceinline__ int nearest(const double *sums, double x, double &dif
     return best;
 }
 
-// Smallest squared distance from x to a subset sum: the same value as the
-// square of the nearest difference (the rounded square is monotone in |d|),
-// without tracking which sum it was.
+// Smallest squared distance from x to a subset sum: the square of the nearest
+// difference, without tracking which sum it was (one subtraction and one
+// minimum with a magnitude per sum).
 template <int K>
 __device__ __forceinline__ double nearest_sq(const double *sums, double x)
 {
-    double d = x - sums[0];
-    double m = d * d;
+    double m = fabs(x - sums[0]);
 #pragma unroll
-    for (int p = 1; p < (1 << K); ++p) {
-        d = x - sums[p];
-        m = fmin(m, d * d);
-    }
-    return m;
+    for (int p = 1; p < (1 << K); ++p)
+        m = fmin(m, fabs(x - sums[p]));
+    return m * m;
 }
 
 __device__ __forceinline__ double wave_min_f64(double v)
@@ -196,6 +197,22 @@ constexpr int ENC_CELLS = 512;                    // chords of the group's g
 constexpr int ENC_RUN = 16;                       // consecutive entries a lane screens
 constexpr int ENC_CHUNK = ENC_RUN * ENC_THREADS;  // entries screened at a time
 constexpr int ENC_LIST = 32;                      // entries scored across the lanes, at most
+// Grids of at most this many subset sums (entries x 2^k) are scored by the
+// definition at once: a few rounds of a lane per entry cost less than the table
+// and the serial scoring of the survivors.  512 x 1024, N(0, 0.02^2), without
+// and with the screening: k = 1, 64 entries 20 / 40 us; k = 2, 32 entries 26 /
+// 29; k = 3, 16 entries 36 / 36; above the line k = 2, 64 entries 26 / 29, but
+// with the cache (256 x 14336) 1050 / 720; k = 3, 32 entries 36 / 33; k = 4, 16
+// entries 47 / 35.
+constexpr int ENC_PLAIN_SUMS = 128;
+// When more sets than this are left after the first one is scored (groups whose
+// entries are nearly alike; at k = 1 most), a lane takes a set and the elements
+// run in order (2^k distances each), instead of one set after the other across
+// the lanes.  512 x 1024, with up to 32 one after the other and with this: k =
+// 1, 1024 entries, N(0, 0.02^2) 106 / 50 us; 32 equal entries 168 / 48 (k = 3),
+// 190 / 69 (k = 4).  With 8 at k = 4, ternary weights with the cache (256 x
+// 14336) took 1342 instead of 1190.
+__host__ __device__ constexpr int enc_serial(int k) { return k == 1 ? 4 : (k == 2 ? 8 : 12); }
 // Two orders of adding 128 non-negative binary64 terms differ by less than
 // this share of their sum (2 x 127 roundings of 2^-53).
 constexpr double ENC_ORDER_EPS = 0x1p-40;
@@ -275,12 +292,13 @@ __device__ __forceinline__ int cell_of(const GroupStats &t, float m2)
 }
 
 // Sorts the group (x0, x1: the lane's two values), takes the order statistics
-// and tabulates g.  With t values below m and P their sum, 2 g(m) = m2 t - 2 P
+// and, for a screened search, tabulates g.  With t values below m and P their sum, 2 g(m) = m2 t - 2 P
 // for m2 = 2 m.
+template <bool SCREENED>
 __device__ GroupStats group_table(EncodeLds &L, float x0, float x1)
 {
     const int lane = threadIdx.x;
-    GroupStats st;
+    GroupStats st = {};
     // bitonic sort of 128 values, sorted value 2 lane + h in v[h]; med3 with
     // an infinity is min or max
     float v0 = x0, v1 = x1;
@@ -308,6 +326,10 @@ __device__ GroupStats group_table(EncodeLds &L, float x0, float x1)
     static_assert(lo % 2 == 0, "both positions in one lane");
     const double q0 = (double)lane_f32(v0, lo / 2), q1 = (double)lane_f32(v1, lo / 2);
     st.q95 = q0 + frac * (q1 - q0);
+    if constexpr (!SCREENED) {
+        __syncthreads();
+        return st;
+    }
 
     // twice the sums of the t smallest values
     double incl = (double)v0 + (double)v1;
@@ -463,15 +485,6 @@ __device__ double score_lanes(EncodeLds &L, const uint16_t *c, bool want, float 
     const int lane = threadIdx.x;
     double mse = __builtin_inf();
     uint64_t left = __ballot(want && !(v > f32_above(ub)));
-    if (__popcll(left) > ENC_LIST) {  // many: a lane per set, the elements in order
-        if (want) {
-            double sums[1 << K];
-            subset_sums<K>(c, sums);
-            mse = entry_mse<K>(L.D, sums);
-        }
-        ub = fmin(ub, wave_min_f64(mse) * (double)GROUP * (1.0 + ENC_ORDER_EPS));
-        return mse;
-    }
     uint32_t w[(K + 1) / 2];
 #pragma unroll
     for (int i = 0; i < (K + 1) / 2; ++i)
@@ -490,14 +503,13 @@ __device__ double score_lanes(EncodeLds &L, const uint16_t *c, bool want, float 
         e1 = nearest_sq<K>(sums, d1);
     };
     double tsum = __builtin_inf();
-    bool first = true;
+    bool first = true, many = false;
     while (left) {
         int q = __ffsll((unsigned long long)left) - 1;
         if (first) {  // the lowest bound first: its error drops most of the others
             const float vm = wave_min_f32((left >> lane) & 1 ? v : __builtin_inff());
             const uint64_t at = __ballot(((left >> lane) & 1) && v == vm);
             q = at ? __ffsll((unsigned long long)at) - 1 : q;
-            first = false;
         }
         double e0, e1;
         terms(q, e0, e1);
@@ -505,8 +517,20 @@ __device__ double score_lanes(EncodeLds &L, const uint16_t *c, bool want, float 
         if (lane == q)
             tsum = s;
         ub = fmin(ub, s * (1.0 + ENC_ORDER_EPS));
-        left &= ~(1ull << q);
         left &= __ballot(!(v > f32_above(ub)));
+        many = first && __popcll(left) > enc_serial(K);  // (the set just scored among them)
+        if (many)
+            break;
+        left &= ~(1ull << q);
+        first = false;
+    }
+    if (many) {  // a lane per set, the elements in order
+        if ((left >> lane) & 1) {
+            double sums[1 << K];
+            subset_sums<K>(c, sums);
+            mse = entry_mse<K>(L.D, sums);
+        }
+        return mse;
     }
     left = __ballot(tsum * (1.0 - ENC_ORDER_EPS) <= ub && tsum < __builtin_inf());
     while (left) {
@@ -545,7 +569,7 @@ __device__ __forceinline__ int wave_min_int(int v)
 
 // Algorithm 1 over the group in L.D (d0, d1: the lane's elements lane and
 // lane + 64; st and L.cell: group_table's).  Every lane returns the same choice.
-template <int K>
+template <int K, bool SCREENED>
 __device__ GroupChoice<K> search_group(const EncodeArgs &a, EncodeLds &L, const GroupStats &st, double d0, double d1)
 {
     const int lane = threadIdx.x;
@@ -581,32 +605,46 @@ __device__ GroupChoice<K> search_group(const EncodeArgs &a, EncodeLds &L, const 
 
     double best_mse = __builtin_inf(), ub = __builtin_inf();  // ub: on the smallest error sum
     int best_e = -1;
-    for (int e0 = 0; e0 < n_entries; e0 += ENC_CHUNK) {
+    if constexpr (!SCREENED) {  // a lane per entry, the elements in order
+        double mse = __builtin_inf();
+        int e = -1;
+        for (int e0 = 0; e0 < n_entries; e0 += ENC_THREADS) {
+            uint16_t c[K];
+            const int ei = e0 + lane;
+            double m = __builtin_inf();
+            if (ei < n_entries && entry_at(ei, c)) {
+                double sums[1 << K];
+                subset_sums<K>(c, sums);
+                m = entry_mse<K>(L.D, sums);
+            }
+            if (m < mse) {
+                mse = m;
+                e = ei;
+            }
+        }
+        best_mse = wave_min_f64(mse);
+        if (best_mse < __builtin_inf())
+            best_e = wave_min_int(mse == best_mse ? e : INT_MAX);
+    }
+    for (int e0 = 0; SCREENED && e0 < n_entries; e0 += ENC_CHUNK) {
         const int left = n_entries - e0;
         const int run = min(ENC_RUN, (left + ENC_THREADS - 1) / ENC_THREADS);
-        // lower bounds of the lane's run of entries
-        float vmin = __builtin_inff();
-        int emin = -1;
-        {
+        // Calls f(i, entry, its coefficients or null where it is not admissible)
+        // for the lane's run of entries.
+        auto walk = [&](auto f) {
             const int e1 = e0 + lane * run;
             int ir = e1 / per_r, js = (e1 / a.n_bias) % a.n_scale, kb = e1 % a.n_bias;
             double s = 0.0;
             EntryShape<K> sh;
             for (int i = 0; i < run; ++i) {
-                float v = __builtin_inff();
+                uint16_t c[K];
+                bool ok = false;
                 if (e1 + i < n_entries) {
                     if (i == 0 || kb == 0) {
                         s = scale_of(js);
                         sh.set(ratio_of(ir), s, a.normalise != 0);
                     }
-                    uint16_t c[K];
-                    if (s > 0.0 && sh.coeffs(bias_of(kb), c)) {
-                        v = entry_bound<K>(L, st, c);
-                        if (emin < 0 || v < vmin) {
-                            vmin = v;
-                            emin = e1 + i;
-                        }
-                    }
+                    ok = s > 0.0 && sh.coeffs(bias_of(kb), c);
                     if (++kb == a.n_bias) {
                         kb = 0;
                         if (++js == a.n_scale) {
@@ -615,9 +653,23 @@ __device__ GroupChoice<K> search_group(const EncodeArgs &a, EncodeLds &L, const 
                         }
                     }
                 }
-                L.lb[i * ENC_THREADS + lane] = v;
+                f(i, e1 + i, ok ? c : (const uint16_t *)nullptr);
             }
-        }
+        };
+        // lower bounds of the lane's run of entries
+        float vmin = __builtin_inff();
+        int emin = -1;
+        walk([&](int i, int e, const uint16_t *c) {
+            float v = __builtin_inff();
+            if (c) {
+                v = entry_bound<K>(L, st, c);
+                if (emin < 0 || v < vmin) {
+                    vmin = v;
+                    emin = e;
+                }
+            }
+            L.lb[i * ENC_THREADS + lane] = v;
+        });
         // the entry with the lowest bound, scored: its error drops most others
         const uint64_t have = __ballot(emin >= 0);
         if (have == 0)  // no admissible entry in this chunk
@@ -659,16 +711,14 @@ __device__ GroupChoice<K> search_group(const EncodeArgs &a, EncodeLds &L, const 
             }
             mse = score_lanes<K>(L, c, lane < n, v, d0, d1, ub);
         } else {  // a lane per entry, the elements in order
-            for (int i = 0; i < run; ++i) {
-                uint16_t c[K];
-                const int ei = e0 + lane * run + i;
+            walk([&](int i, int ei, const uint16_t *c) {
                 double m = __builtin_inf();
-                if (kept(i) && entry_at(ei, c)) {
+                if (c && kept(i)) {
                     double sums[1 << K];
                     subset_sums<K>(c, sums);
                     double err = 0.0;
                     for (int j0 = 0; j0 < GROUP && err <= ub; j0 += 16)
-#pragma unroll 4
+#pragma unroll(K <= 2 ? 16 : 4)
                         for (int j = j0; j < j0 + 16; ++j)
                             err += nearest_sq<K>(sums, L.D[j]);
                     if (err <= ub)  // (else it can neither win nor tie)
@@ -679,7 +729,7 @@ __device__ GroupChoice<K> search_group(const EncodeArgs &a, EncodeLds &L, const 
                     e = ei;
                 }
                 ub = fmin(ub, wave_min_f64(m) * (double)GROUP);
-            }
+            });
         }
         // smallest error, lowest entry index among equal errors
         const double m = wave_min_f64(mse);
@@ -732,7 +782,7 @@ __device__ __forceinline__ void store_group(const EncodeArgs &a, size_t grp, con
         a.mse[grp] = mse;
 }
 
-template <int K>
+template <int K, bool SCREENED>
 __global__ void __launch_bounds__(ENC_THREADS) encode_kernel(EncodeArgs a)
 {
     __shared__ EncodeLds L;
@@ -746,8 +796,8 @@ __global__ void __launch_bounds__(ENC_THREADS) encode_kernel(EncodeArgs a)
     const double d0 = (double)x0, d1 = (double)x1;
     L.D[lane] = d0;
     L.D[lane + 64] = d1;
-    const GroupStats st = group_table(L, x0, x1);
-    const GroupChoice<K> r = search_group<K>(a, L, st, d0, d1);
+    const GroupStats st = group_table<SCREENED>(L, x0, x1);
+    const GroupChoice<K> r = search_group<K, SCREENED>(a, L, st, d0, d1);
     store_group<K>(a, grp, r.c, d0, d1, r.mse);
 }
 
@@ -762,7 +812,7 @@ __global__ void __launch_bounds__(ENC_THREADS) encode_kernel(EncodeArgs a)
 // count), otherwise the full search runs and its choice enters the cache
 // (the no-admissible-entry fallback does not).  The first group of a row
 // always searches; with slots = 0 the result is the plain encoder's.
-template <int K>
+template <int K, bool SCREENED>
 __global__ void __launch_bounds__(ENC_THREADS) encode_cached_kernel(EncodeArgs a, int slots, uint8_t *hits)
 {
     __shared__ EncodeLds L;
@@ -784,7 +834,7 @@ __global__ void __launch_bounds__(ENC_THREADS) encode_cached_kernel(EncodeArgs a
         __syncthreads();  // the previous group's reads of L are done
         L.D[lane] = d0;
         L.D[lane + 64] = d1;
-        const GroupStats st = group_table(L, x0, x1);
+        const GroupStats st = group_table<SCREENED>(L, x0, x1);
         bool hit = false;
         uint16_t c[K];
         double mse = 0.0;
@@ -792,7 +842,7 @@ __global__ void __launch_bounds__(ENC_THREADS) encode_cached_kernel(EncodeArgs a
             const double avg = mse_sum / (double)g;
             // a set whose lower bound is above the mean cannot be taken
             const bool held = lane < n_cached;
-            const float v = held ? entry_bound<K>(L, st, cs) : __builtin_inff();
+            const float v = held ? (SCREENED ? entry_bound<K>(L, st, cs) : -3e38f) : __builtin_inff();
             double ub = avg * (double)GROUP;
             const double m = score_lanes<K>(L, cs, held, v, d0, d1, ub);
             const double best = wave_min_f64(m);
@@ -807,7 +857,7 @@ __global__ void __launch_bounds__(ENC_THREADS) encode_cached_kernel(EncodeArgs a
             }
         }
         if (!hit) {
-            const GroupChoice<K> r = search_group<K>(a, L, st, d0, d1);
+            const GroupChoice<K> r = search_group<K, SCREENED>(a, L, st, d0, d1);
 #pragma unroll
             for (int i = 0; i < K; ++i)
                 c[i] = r.c[i];
@@ -830,15 +880,28 @@ __global__ void __launch_bounds__(ENC_THREADS) encode_cached_kernel(EncodeArgs a
     }
 }
 
+// The kernel (KERNEL<K, SCREENED>) for k planes and the grid of a.
+#define SBVR_ENCODE_KERNEL(KERNEL, k, screened)                                                                \
+    ((screened) ? ((k) == 4   ? (const void *)KERNEL<4, true>                                                  \
+                   : (k) == 3 ? (const void *)KERNEL<3, true>                                                  \
+                   : (k) == 2 ? (const void *)KERNEL<2, true>                                                  \
+                              : (const void *)KERNEL<1, true>)                                                 \
+                : ((k) == 4   ? (const void *)KERNEL<4, false>                                                 \
+                   : (k) == 3 ? (const void *)KERNEL<3, false>                                                 \
+                   : (k) == 2 ? (const void *)KERNEL<2, false>                                                 \
+                              : (const void *)KERNEL<1, false>))
+
+static bool screened(const EncodeArgs &a, int k)
+{
+    return ((a.n_ratio1 + a.n_ratio2) * a.n_scale * a.n_bias) << k > ENC_PLAIN_SUMS;
+}
+
 int launch_encode(int O, int I, int k, const float *W, int n_ratio1, int n_ratio2, int n_scale, int n_bias,
                   int normalise, uint32_t *planes, uint16_t *coeffs, double *mse, hipStream_t stream)
 {
     EncodeArgs a = {W, planes, coeffs, mse, O, I, n_ratio1, n_ratio2, n_scale, n_bias, normalise};
     const size_t groups = (size_t)O * (I / GROUP);
-    const void *fn = k == 4   ? (const void *)encode_kernel<4>
-                     : k == 3 ? (const void *)encode_kernel<3>
-                     : k == 2 ? (const void *)encode_kernel<2>
-                              : (const void *)encode_kernel<1>;
+    const void *fn = SBVR_ENCODE_KERNEL(encode_kernel, k, screened(a, k));
     void *args[] = {&a};
     return launch_kernel(fn, dim3((unsigned)groups), dim3(ENC_THREADS), 0, stream, args);
 }
@@ -848,10 +911,7 @@ int launch_encode_cached(int O, int I, int k, const float *W, int n_ratio1, int 
                          hipStream_t stream)
 {
     EncodeArgs a = {W, planes, coeffs, mse, O, I, n_ratio1, n_ratio2, n_scale, n_bias, normalise};
-    const void *fn = k == 4   ? (const void *)encode_cached_kernel<4>
-                     : k == 3 ? (const void *)encode_cached_kernel<3>
-                     : k == 2 ? (const void *)encode_cached_kernel<2>
-                              : (const void *)encode_cached_kernel<1>;
+    const void *fn = SBVR_ENCODE_KERNEL(encode_cached_kernel, k, screened(a, k));
     void *args[] = {&a, &slots, &hits};
     return launch_kernel(fn, dim3((unsigned)O), dim3(ENC_THREADS), 0, stream, args);
 }

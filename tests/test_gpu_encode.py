@@ -115,6 +115,22 @@ def test_encoder_screening_keeps_the_minimum(sb, kind):
     assert_same_cached(sb, W, 4, 64, what=kind)
 
 
+@pytest.mark.parametrize("k", [1, 2, 3, 4])
+@pytest.mark.parametrize("kind", ["gauss", "ternary", "all_entries_equal", "clusters"])
+def test_encoder_grids_around_the_screening(sb, kind, k):
+    """Grids of a few entries: at most 128 subset sums (entries x 2^k) are scored
+    without the screening, above that up to 32 entries go through the scoring of
+    the survivors, where sets that are left after the first one are scored one
+    after the other (up to 4, 8 or 12 of them) or a lane each."""
+    rng = np.random.default_rng(19)
+    W = 0.02 * rng.standard_normal(4 * 512) if kind == "gauss" else screening_rows(kind, 4 * 512, rng)
+    W = W.astype(np.float32).reshape(4, 512)
+    n = 128 >> k  # entries of the largest grid without the screening
+    for grid in ((1, 1, 1, 1), (1, 1, n // 2, 1), (1, n, 1, 1), (1, 1, 3, 2), (1, 1, 13, 1), (1, 1, 16, 1),
+                 (1, 2, 11, 1), (13, 20, 2, 1), (2, 3, 13, 1)):
+        assert_same(sb, W, k, oracle.SearchParams(*grid), what=f"{kind} {grid}")
+
+
 def test_encoder_output_gemv_parity(sb):
     """The GPU-encoded matrix through the GPU GEMV against the oracle's exact
     GEMV of the same encoding."""
@@ -229,6 +245,31 @@ def test_cached_encoder_degenerate_rows_and_grids(sb):
     D = synth.weights(1, 128, 0.02, seed=5)[0]
     h = assert_same_cached(sb, np.tile(D, 3)[None, :].astype(np.float32), 4, 8, what="identical groups")
     assert not h.any()
+
+
+@pytest.mark.parametrize("slots", [40, 64])
+@pytest.mark.parametrize("k", [1, 2, 3, 4])
+def test_cached_encoder_many_held_sets(sb, k, slots):
+    """Rows of 14336 columns (112 groups) whose groups grow, so that each misses
+    (its error is above the mean of the ones before), until every slot is held
+    and sets are replaced.  Zero groups in between score zero with every set
+    held, which keeps all of them to the last comparison (the oldest is taken);
+    groups far below the earlier ones keep many.  Grids with and without the
+    screening."""
+    rng = np.random.default_rng(100 * k + slots)
+    scale = 0.002 * 1.05 ** np.arange(112)
+    W = rng.standard_normal((3, 112, 128)) * scale[:, None]
+    easy = {35: 0.0, 36: 1e-4, 71: 0.0, 72: 0.002, 100: 0.0, 101: 1e-30, 111: 0.0}
+    for g, s in easy.items():
+        W[:, g] = s * rng.standard_normal((3, 128))
+    W[2] = np.abs(W[2])  # one-sided groups
+    W = W.reshape(3, -1).astype(np.float32)
+    for params in (oracle.DEFAULT, oracle.SearchParams(1, 1, 4, 2)):
+        h = assert_same_cached(sb, W, k, slots, params, what=f"many held sets {params}")
+        if params is oracle.DEFAULT:
+            assert (h[:, :71] == 0).sum(1).min() > 48  # sets held at the second zero group, if there is a slot
+            assert (h == 0).sum(1).min() > slots        # and some replaced
+            assert h[:, [71, 100, 111]].all()
 
 
 def test_cached_encoder_full_size_and_indexed_gemv(sb):
