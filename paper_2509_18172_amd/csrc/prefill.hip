@@ -493,23 +493,24 @@ __global__ void __launch_bounds__(64 * NW) prefill_short_kernel(PrefillArgs a)
 // for n wavefronts and x loads of four tokens per group.  The shape with the
 // lowest cost runs.
 //
-// Fitted on MI355X to the times of all twelve shapes on 3949 matrices and
+// Fitted on MI355X to the times of all twelve shapes on 6719 matrices and
 // prompts (1 .. 28672 rows, 128 .. 28672 columns, 1 .. 2048 tokens, k = 1 .. 4,
 // the sizes spread over their logarithms; each shape forced in turn, 2 to 40
 // launches back to back over rotating weights): a non-negative least-squares
 // fit of the relative error, then single steps of the constants that lower the
 // time of the chosen shape over the best one's.  k is left out: constants of
-// each k's own gained 0.1 %.  The choice takes 0.9 % more than the best shape
-// on average (6.1 % at the 95th percentile, 23 % at most; constants fitted to
-// 70 % of the cases, 0.9 % on the others).  Against the LDS-table kernels it
-// takes 0.64 (k = 1) to 0.54 (k = 3) of the time (geometric means); 2 of the
-// 3949 are slower, by 4 and 5 % (163 x 5632, 2038 tokens, and 15846 x 1408, 16
-// tokens, both k = 1).
-// What the terms are for: a fit without the rounds took a shape that a CU holds
-// once for one that shares it (18332 x 896, k = 2, 23 tokens 16.2 us instead of
-// 8.5; 11.4 with the LDS tables), and without the shape of 32 tokens and eight
-// row groups matrices of one group took up to 1.29 times the LDS tables' time
-// (6599 x 128, k = 1, 265 tokens 6.6 us instead of 4.1).
+// each k's own gained 0.1 %.  On 2757 further cases the choice takes 0.9 % more
+// than the best shape on average (5.8 % at the 95th percentile, 24 % at most);
+// a fit without the rounds (and with a shape less) took 2.7 % more, the present
+// one is slower than it by over 3 % on 1.3 % of the cases (21 % at most).
+// Against the LDS-table kernels it takes 0.65 / 0.58 / 0.54 / 0.56 of the time at
+// k = 1 / 2 / 3 / 4 (geometric means over all 9476); 2 are slower by more than 2 %
+// (15846 x 1408, k = 1, 16 tokens, 9 %; 163 x 5632, k = 1, 2038 tokens, 4 %).
+// What the terms are for: without the rounds a shape that a CU holds once was
+// taken for one that shares it (18332 x 896, k = 2, 23 tokens 16.2 us; 11.4 with
+// the LDS tables, 8.5 with the best shape), and without the shape of 32 tokens
+// and eight row groups matrices of one group took up to 1.29 times the LDS
+// tables' time (6599 x 128, k = 1, 265 tokens 6.6 us instead of 4.1).
 struct PrefillShape {
     int rt, tt, r, st;
     int held;  // prefill_kernel: workgroups a CU holds at once (the short kernel's: see prefill_cost)
@@ -517,18 +518,18 @@ struct PrefillShape {
 };
 
 static const PrefillShape PREFILL_SHAPES[] = {
-    {0, 1, 8, 1, 0, {1.811f, 0.268f, 0.509f, 0.377f, 0.164f, 0.226f, 0.000f, 0.060f, 0.379f}},
-    {0, 1, 16, 1, 0, {1.639f, 0.038f, 0.819f, 0.015f, 0.452f, 0.332f, 0.001f, 0.097f, 0.613f}},
-    {0, 2, 8, 1, 0, {1.247f, 0.310f, 0.333f, 0.674f, 0.344f, 0.001f, 0.002f, 0.075f, 0.915f}},
-    {1, 1, 1, 1, 1, {0.426f, 0.282f, 0.704f, 0.324f, 2.808f}},
-    {1, 2, 1, 2, 1, {0.010f, 0.004f, 1.727f, 0.025f, 4.068f}},
-    {1, 2, 2, 1, 1, {0.495f, 0.000f, 1.119f, 0.426f, 3.393f}},
-    {1, 2, 4, 1, 2, {1.901f, 0.359f, 0.508f, 0.615f, 1.448f, 0.140f, 0.813f}},
-    {1, 4, 2, 2, 1, {0.031f, 0.019f, 1.361f, 1.114f, 8.276f}},
-    {1, 4, 4, 1, 1, {2.741f, 0.027f, 1.088f, 0.987f, 4.261f}},
-    {1, 4, 8, 1, 1, {1.877f, 0.013f, 1.297f, 0.565f, 4.058f}},
-    {1, 1, 8, 1, 2, {1.871f, 0.604f, 0.210f, 0.414f, 1.210f, 0.002f, 0.000f}},
-    {2, 4, 8, 1, 1, {0.210f, 0.008f, 0.904f, 2.695f, 10.764f}},
+    {0, 1, 8, 1, 0, {1.810f, 0.268f, 0.509f, 0.378f, 0.164f, 0.234f, 0.000f, 0.060f, 0.381f}},
+    {0, 1, 16, 1, 0, {1.670f, 0.034f, 0.831f, 0.016f, 0.457f, 0.301f, 0.000f, 0.089f, 0.616f}},
+    {0, 2, 8, 1, 0, {1.250f, 0.316f, 0.339f, 0.669f, 0.345f, 0.000f, 0.000f, 0.074f, 0.920f}},
+    {1, 1, 1, 1, 1, {0.392f, 0.305f, 0.703f, 0.355f, 2.736f}},
+    {1, 2, 1, 2, 1, {0.147f, 0.007f, 1.106f, 1.079f, 3.932f}},
+    {1, 2, 2, 1, 1, {0.801f, 0.004f, 0.758f, 0.721f, 4.110f}},
+    {1, 2, 4, 1, 2, {1.949f, 0.366f, 0.467f, 0.483f, 1.493f, 0.153f, 0.593f}},
+    {1, 4, 2, 2, 1, {0.043f, 0.165f, 1.262f, 0.889f, 7.315f}},
+    {1, 4, 4, 1, 1, {2.572f, 0.012f, 1.107f, 0.835f, 3.777f}},
+    {1, 4, 8, 1, 1, {1.142f, 0.001f, 1.241f, 0.524f, 4.299f}},
+    {1, 1, 8, 1, 2, {1.859f, 0.490f, 0.215f, 0.480f, 1.189f, 0.001f, 0.002f}},
+    {2, 4, 8, 1, 1, {0.698f, 0.001f, 0.869f, 2.719f, 9.087f}},
 };
 
 // LDS of a launch: two activation stages per K-slice, which the partial sums

@@ -40,15 +40,19 @@ def test_shape_cases_take_every_shape(k):
     assert any(T % 16 == 0 for T in full) and any(T < 16 for T in full) and any(T > 16 and T % 16 for T in full)
 
 
-@pytest.mark.parametrize("O,I,k,T,best", [
-    # 16.2, 9.7 and 10.3 us with the 32-token tiles of the 16-row kernel, whose
-    # workgroups a CU holds one at a time; 8.5, 7.4 and 6.7 with these
-    (18332, 896, 2, 23, (1, 2, 4)), (12011, 1024, 2, 26, (1, 2, 2)), (10710, 896, 1, 25, (1, 2, 2)),
-    # single groups: 6.6, 5.8 and 5.4 us with several K-slices or 128-token
-    # tiles, 4.1, 3.9 and 3.7 with this
-    (6599, 128, 1, 265, (1, 1, 8)), (14088, 128, 1, 107, (1, 1, 8)), (8344, 128, 1, 91, (1, 1, 8))])
-def test_calls_keep_a_fast_shape(O, I, k, T, best):
-    assert shape(O, I, k, T) == index(*best)
+# Times on MI355X of the calls a rule that ignored the rounds sent to the 32-token
+# tiles of the 16-row kernel, whose workgroups a CU holds one at a time: 16.2, 9.7
+# and 10.3 us; the best shapes take 8.5, 7.4 and 6.7.
+@pytest.mark.parametrize("O,I,k,T", [(18332, 896, 2, 23), (12011, 1024, 2, 26), (10710, 896, 1, 25)])
+def test_rounds_count(O, I, k, T):
+    assert shape(O, I, k, T) != SHORT_32_TOKENS
+
+
+# 6.6, 5.8 and 5.4 us with several K-slices or 128-token tiles, 4.1, 3.9 and 3.7
+# with a single K-slice and 32 tokens.
+@pytest.mark.parametrize("O,T", [(6599, 265), (14088, 107), (8344, 91)])
+def test_single_groups_over_many_tokens(O, T):
+    assert shape(O, 128, 1, T) == index(1, 1, 8)
 
 
 def test_longest_prompts_have_a_shape():
