@@ -45,9 +45,10 @@ __device__ __forceinline__ uint16_t f64_to_f16_rne(double x)
     return (uint16_t)(sign | (uint32_t)q);  // q == 0x400 is the smallest normal
 }
 
-// The same value for finite x without branches: binary32 toward zero with the
-// lost bits kept in its last one (24 bits, 13 more than binary16's), which the
-// hardware's one rounding to binary16 then treats as the exact value.
+// The same value for finite x without branches, by rounding to odd (Boldo and
+// Melquiond's double rounding): binary32 toward zero with the lost bits kept in
+// its last one (24 bits, 13 more than binary16's), which the hardware's one
+// rounding to binary16 then treats as the exact value.
 __device__ __forceinline__ uint16_t f64_to_f16_odd(double x)
 {
     const float f = (float)x;

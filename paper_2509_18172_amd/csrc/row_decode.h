@@ -5,8 +5,9 @@
 // holds the row's 2^k sums as bytes, low and high ones apart, in up to eight
 // registers; byte permutes then look up four weights at a time.  Against a
 // table in LDS, one read per weight, this trades about 2 vector instructions
-// per weight for the LDS reads, whose bank conflicts (random entries, 11 LDS
-// cycles per 64 lookups) bounded the prefill kernels.
+// per weight for the LDS reads, whose bank conflicts (random entries, about 6
+// LDS cycles per 64 lookups, shared by a CU's four SIMDs) bounded the prefill
+// kernels.
 #pragma once
 
 #include "device_ops.h"
